@@ -228,10 +228,11 @@ struct JoinerBwdWs {
   int* frame_nt;
   int* frame_p;
   int4* rowinfo;
-  uint16_t* dl[2];
+  uint16_t *dl[2], *dc[2];
+  float* dc_inv[2];
   uint16_t* wn;
   uint16_t* wt;
-  float *wn_inv, *wt_inv, *dlmax;
+  float *wn_inv, *wt_inv, *rsc;
   float* dpre[2];
   float* enc_part;
   uint16_t* hbuf[3];
@@ -256,14 +257,19 @@ JoinerBwdWs joiner_bwd_layout(void* base, int N, int T, int S, int J, int V, int
   w.frame_p = c.take<int>((size_t)N * T);
   w.rowinfo = c.take<int4>(M);
   const size_t ldh = joiner_words(J, bf16), ldd = joiner_words(V, bf16);
-  // rings of chunk buffers: 2 slots of d(logits), 3 of h (1 of each when one_slot)
-  for (int k = 0; k < 2; ++k) w.dl[k] = one_slot && k > 0 ? w.dl[0] : c.take<uint16_t>(w.chunk_rows * ldd);
+  // rings of chunk buffers: 2 slots of d(logits) (split: of both its forms), 3 of h (1 of each when one_slot)
+  for (int k = 0; k < 2; ++k) {
+    const bool first = one_slot && k > 0;
+    w.dl[k] = first ? w.dl[0] : c.take<uint16_t>(w.chunk_rows * ldd);
+    w.dc[k] = bf16 ? w.dl[k] : first ? w.dc[0] : c.take<uint16_t>(w.chunk_rows * ldd);
+    w.dc_inv[k] = bf16 ? nullptr : first ? w.dc_inv[0] : c.take<float>((size_t)joiner_db_rows(w.chunk_rows) * joiner_ldl(V));
+  }
   for (int k = 0; k < 3; ++k) w.hbuf[k] = one_slot && k > 0 ? w.hbuf[0] : c.take<uint16_t>(w.chunk_rows * ldh);
   w.wn = joiner_w_copy(V, bf16) ? c.take<uint16_t>(J * ldd) : nullptr;
   w.wt = c.take<uint16_t>(V * ldh);
   w.wn_inv = bf16 ? nullptr : c.take<float>((size_t)J);
   w.wt_inv = bf16 ? nullptr : c.take<float>((size_t)V);
-  w.dlmax = bf16 ? nullptr : c.take<float>((size_t)joiner_dlmax_parts());
+  w.rsc = bf16 ? nullptr : c.take<float>(M);
   for (int k = 0; k < 2; ++k) w.dpre[k] = one_slot && k > 0 ? w.dpre[0] : c.take<float>((size_t)w.chunk_rows * J);
   w.enc_part = c.take<float>((M + 127) / 128 * 2 * J);
   w.dw_part = c.take<float>((size_t)w.splits * J * V);
@@ -365,16 +371,20 @@ void set_joiner_bwd(JoinerArgs& a, const JoinerBwdWs& w, const float* lse, const
   a.ldh = joiner_words(a.J, a.bf16);
   a.ldd = joiner_words(a.V, a.bf16);
   a.dl = w.dl[0];
+  a.dc = w.dc[0];
+  a.dc_inv = w.dc_inv[0];
   for (int k = 0; k < 3; ++k) a.hring[k] = w.hbuf[k];
   for (int k = 0; k < 2; ++k) {
     a.dlring[k] = w.dl[k];
+    a.dcring[k] = w.dc[k];
+    a.dcinvring[k] = w.dc_inv[k];
     a.dpring[k] = w.dpre[k];
   }
   a.wn = w.wn ? w.wn : static_cast<uint16_t*>(const_cast<void*>(a.W));  // read only there
   a.wt = w.wt;
   a.wn_inv = w.wn_inv;
   a.wt_inv = w.wt_inv;
-  a.dlmax = w.dlmax;
+  a.rsc = w.rsc;
   a.ldl = joiner_ldl(a.V);
   a.chunk_rows = w.chunk_rows;
   a.dpre = w.dpre[0];

@@ -291,14 +291,12 @@ DEV void split_f16x2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
   lo = (uint32_t)l0 | ((uint32_t)l1 << 16);
 }
 
-// The power of two that brings |x| <= mx to at most 2^14 (1 for an operand
-// with no finite non-zero element), clamped so that it and its inverse are
-// normal numbers (elements below 2^-100 of 1 lose their low bits).
+// The power of two that brings |x| <= mx to [2^13, 2^14), at most 2^100, so
+// that it and its inverse are normal numbers (elements below 2^-100 of 1 lose
+// their low bits). mx >= 0, infinity included, no NaN.
 DEV float split_scale(float mx) {
-  if (!(mx > 0.f)) return 1.f;
-  const int e = (int)((__float_as_uint(mx) >> 23) & 0xff) - 127;  // 2^e <= mx < 2^(e+1) (denormals: -127)
-  const int q = min(13 - e, 100);
-  return __uint_as_float((uint32_t)(q + 127) << 23);
+  const uint32_t e = max(__float_as_uint(mx) >> 23, 40u);  // biased
+  return __uint_as_float((13u + 2 * 127u - e) << 23);
 }
 DEV float finite_abs(float x) {
   const float a = __builtin_fabsf(x);
@@ -488,10 +486,13 @@ struct TrCfg {
   static constexpr int FM = WM / 16, FN = WN / 16;
   static constexpr int A_ROWB = BM * XP * 2, B_ROWB = BN * XP * 2;  // bytes per LDS row
   static constexpr int A_BYTES = BK * A_ROWB, B_BYTES = BK * B_ROWB;
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
+  // split: the factors of B's columns in this K-step (one wave-wide load, whose last half is past the columns)
+  static constexpr int F_BYTES = SPLIT ? 1024 : 0;
+  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + F_BYTES;
   static constexpr int SMEM_BYTES = 2 * STAGE_BYTES;
   static constexpr int A_IPW = A_BYTES / 1024 / NW, B_IPW = B_BYTES / 1024 / NW;  // loads per wave per stage
   static_assert(A_ROWB % 256 == 0 && B_ROWB % 256 == 0, "whole swizzle blocks per row");
+  static_assert(!SPLIT || BN * 4 <= F_BYTES, "the factors are one load");
   static_assert(A_BYTES / 1024 % NW == 0 && B_BYTES / 1024 % NW == 0, "whole loads per wave");
 };
 
@@ -501,6 +502,16 @@ struct TrCfg {
 struct TrSrc {
   const unsigned char* base;
   int rows, ld, c0;
+};
+
+// The factors of a split B operand's columns, [K-step][ld] from `base` on, for
+// columns [c0, ld) (zeros past ld): B's planes are scaled by a power of two of
+// their own in every column of a K-step's rows, undone as the K-step's products
+// join the sum, so that neither a small column nor a small group of rows runs
+// out of fp16's range beside large ones.
+struct TrFactors {
+  const float* base;
+  int ld, c0;
 };
 
 // An operand tile's rows from r0 on: the resource starts there, so that 32-bit
@@ -538,7 +549,8 @@ DEV F tr_frag(const unsigned char* p) {
 }
 
 template <class Cfg>
-DEV void tr_compute_stage(const unsigned char* As, const unsigned char* Bs, floatx4 (&acc)[Cfg::FM][Cfg::FN]) {
+DEV void tr_compute_stage(const unsigned char* As, const unsigned char* Bs, const float* fac,
+                          floatx4 (&acc)[Cfg::FM][Cfg::FN]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / Cfg::WGN, wn = wave % Cfg::WGN;
   const int row = lane >> 2, key = row & 7;  // rows 0..15 of a fragment, 4 lanes a row
@@ -547,26 +559,34 @@ DEV void tr_compute_stage(const unsigned char* As, const unsigned char* Bs, floa
   // pair of 16-column block c: its 32 bytes in bf16; its hi plane when split
   // (the lo plane two pairs on)
   auto pair = [](int c) { return Cfg::SPLIT ? (c >> 1) * 4 + (c & 1) : c; };
+  if constexpr (Cfg::SPLIT) {
+    static_assert(Cfg::BK == 32, "one factor per column and K-step");
+    f16x8 ah[Cfg::FM], al[Cfg::FM];
 #pragma unroll
-  for (int ks = 0; ks < Cfg::BK; ks += 32) {
-    if constexpr (Cfg::SPLIT) {
-      f16x8 ah[Cfg::FM], al[Cfg::FM], bh[Cfg::FN], bl[Cfg::FN];
+    for (int i = 0; i < Cfg::FM; ++i) {
+      al[i] = tr_frag<f16x8, Cfg::A_ROWB>(a + (((pair(wm * Cfg::FM + i) + 2) ^ key) << 5));
+      ah[i] = tr_frag<f16x8, Cfg::A_ROWB>(a + ((pair(wm * Cfg::FM + i) ^ key) << 5));
+    }
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j) {
+      const f16x8 bh = tr_frag<f16x8, Cfg::B_ROWB>(b + ((pair(wn * Cfg::FN + j) ^ key) << 5));
+      const f16x8 bl = tr_frag<f16x8, Cfg::B_ROWB>(b + (((pair(wn * Cfg::FN + j) + 2) ^ key) << 5));
+      const floatx4 f = *reinterpret_cast<const floatx4*>(fac + out_col<Cfg>(j));
+      floatx4 t[Cfg::FM];
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bh, al[i], floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bl, ah[i], t[i], 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(bh, ah[i], t[i], 0, 0, 0);
 #pragma unroll
       for (int i = 0; i < Cfg::FM; ++i)
-        al[i] = tr_frag<f16x8, Cfg::A_ROWB>(a + ks * Cfg::A_ROWB + (((pair(wm * Cfg::FM + i) + 2) ^ key) << 5));
 #pragma unroll
-      for (int j = 0; j < Cfg::FN; ++j)
-        bh[j] = tr_frag<f16x8, Cfg::B_ROWB>(b + ks * Cfg::B_ROWB + ((pair(wn * Cfg::FN + j) ^ key) << 5));
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaf(t[i][r], f[r], acc[i][j][r]);
+    }
+  } else {
 #pragma unroll
-      for (int i = 0; i < Cfg::FM; ++i)
-        ah[i] = tr_frag<f16x8, Cfg::A_ROWB>(a + ks * Cfg::A_ROWB + ((pair(wm * Cfg::FM + i) ^ key) << 5));
-#pragma unroll
-      for (int j = 0; j < Cfg::FN; ++j)
-        bl[j] = tr_frag<f16x8, Cfg::B_ROWB>(b + ks * Cfg::B_ROWB + (((pair(wn * Cfg::FN + j) + 2) ^ key) << 5));
-      mfma_f16<Cfg>(al, bh, acc);
-      mfma_f16<Cfg>(ah, bl, acc);
-      mfma_f16<Cfg>(ah, bh, acc);
-    } else {
+    for (int ks = 0; ks < Cfg::BK; ks += 32) {
       bf16x8 fa[Cfg::FM], fb[Cfg::FN];
 #pragma unroll
       for (int i = 0; i < Cfg::FM; ++i)
@@ -579,23 +599,34 @@ DEV void tr_compute_stage(const unsigned char* As, const unsigned char* Bs, floa
   }
 }
 
+// One K-step's rows of both operands, and its factors, into a stage.
+template <class Cfg>
+DEV void tr_fetch_stage(const TrSrc& sa, const TrSrc& sb, const TrFactors& f, int kt, unsigned char* st) {
+  tr_fetch<Cfg::A_IPW, Cfg::A_ROWB>(sa, kt * Cfg::BK, st);
+  tr_fetch<Cfg::B_IPW, Cfg::B_ROWB>(sb, kt * Cfg::BK, st + Cfg::A_BYTES);
+  if constexpr (Cfg::SPLIT) {
+    if (threadIdx.x < 64) {
+      const Rsrc rs = make_rsrc(f.base + (size_t)kt * f.ld, (size_t)f.ld * 4);
+      const int c = 4 * (int)threadIdx.x;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LdsPtr)(st + Cfg::A_BYTES + Cfg::B_BYTES), 16,
+                                               c < Cfg::BN ? (uint32_t)(f.c0 + c) * 4u : kOob, 0, 0, 0);
+    }
+  }
+}
+
 // K loop over all rows of the sources: as gemm_mainloop_lds.
 template <class Cfg>
-DEV void gemm_mainloop_tr(const TrSrc& sa, const TrSrc& sb, unsigned char* smem, floatx4 (&acc)[Cfg::FM][Cfg::FN]) {
+DEV void gemm_mainloop_tr(const TrSrc& sa, const TrSrc& sb, const TrFactors& f, unsigned char* smem,
+                          floatx4 (&acc)[Cfg::FM][Cfg::FN]) {
   zero_acc<Cfg>(acc);
   const int nk = (sa.rows + Cfg::BK - 1) / Cfg::BK;
   if (nk <= 0) return;
-  tr_fetch<Cfg::A_IPW, Cfg::A_ROWB>(sa, 0, smem);
-  tr_fetch<Cfg::B_IPW, Cfg::B_ROWB>(sb, 0, smem + Cfg::A_BYTES);
+  tr_fetch_stage<Cfg>(sa, sb, f, 0, smem);
   for (int kt = 0; kt < nk; ++kt) {
     lds_stage_barrier();
-    if (kt + 1 < nk) {
-      unsigned char* st = smem + ((kt + 1) & 1) * Cfg::STAGE_BYTES;
-      tr_fetch<Cfg::A_IPW, Cfg::A_ROWB>(sa, (kt + 1) * Cfg::BK, st);
-      tr_fetch<Cfg::B_IPW, Cfg::B_ROWB>(sb, (kt + 1) * Cfg::BK, st + Cfg::A_BYTES);
-    }
+    if (kt + 1 < nk) tr_fetch_stage<Cfg>(sa, sb, f, kt + 1, smem + ((kt + 1) & 1) * Cfg::STAGE_BYTES);
     const unsigned char* cs = smem + (kt & 1) * Cfg::STAGE_BYTES;
-    tr_compute_stage<Cfg>(cs, cs + Cfg::A_BYTES, acc);
+    tr_compute_stage<Cfg>(cs, cs + Cfg::A_BYTES, reinterpret_cast<const float*>(cs + Cfg::A_BYTES + Cfg::B_BYTES), acc);
   }
   __syncthreads();
 }

@@ -317,32 +317,12 @@ DEV void prep_wt_split(const JoinerArgs& a, int b) {
   }
 }
 
-// fp32 backward: the largest |scale| (|gx| + |gy|) over the present slots,
-// which bounds |d(logits)|, as kDlMaxParts partial maxima.
-constexpr int kDlMaxParts = 256;
-DEV void prep_dlmax(const JoinerArgs& a, int b) {
-  __shared__ float s_max[kPrepThreads / 64];
-  const int T = a.b.T, S = a.S;
-  const size_t total = (size_t)a.b.N * T * S;
-  float m = 0.f;
-  for (size_t i = (size_t)b * kPrepThreads + threadIdx.x; i < total; i += (size_t)kDlMaxParts * kPrepThreads) {
-    const int n = (int)(i / ((size_t)T * S)), t = (int)(i - (size_t)n * T * S) / S;
-    int Tn, Un;
-    utt_dims(a.b, n, Tn, Un);
-    const int u = a.ranges[i];
-    const float g = finite_abs(a.gxo[i]) + finite_abs(a.gyo[i]);
-    if (t < Tn && u >= 0 && u <= Un) m = fmaxf(m, finite_abs(g * (a.scale ? a.scale[n] : 1.f)));
-  }
-  m = wave_max_f(m);
-  if ((threadIdx.x & 63) == 0) s_max[threadIdx.x >> 6] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) a.dlmax[b] = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
-}
-// The scale of the d(logits) planes, from the partial maxima (every wave by itself).
-DEV float dl_scale(const JoinerArgs& a) {
-  static_assert(kDlMaxParts == 256, "four partial maxima per lane");
-  const float4 v = reinterpret_cast<const float4*>(a.dlmax)[threadIdx.x & 63];
-  return split_scale(wave_max_f(fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w))));
+// fp32 backward: the scale of a row's d(logits) planes, from the bound
+// |scale| (|gx| + |gy|) (softmax <= 1), so that every row keeps fp32's
+// relative precision whatever its utterance's scale and its occupations.
+DEV float row_scale(const JoinerArgs& a, int n, size_t nts) {
+  const float g = finite_abs(a.gxo[nts]) + finite_abs(a.gyo[nts]);
+  return split_scale(finite_abs(g * (a.scale ? a.scale[n] : 1.f)));
 }
 
 // Blocks of the prep kernel after those of the utterances, and the column
@@ -351,7 +331,7 @@ DEV float dl_scale(const JoinerArgs& a) {
 // rows below hrows: its first chunk), so that the h pass takes no launch of
 // its own.
 struct PrepBlocks {
-  int wn, wt, dlmax;
+  int wn, wt;
   int hj, hrows;
 };
 constexpr int kPrepHGroups = 8;  // 8-column groups of a row per block
@@ -370,12 +350,8 @@ __global__ __launch_bounds__(kPrepThreads) void joiner_prep_kernel(JoinerArgs a,
       return;
     }
     b -= pb.wt;
-    if (b < pb.wn) {
-      if constexpr (SP) prep_wn_split(a, b);
-      else prep_wpad(a, b);
-      return;
-    }
-    if constexpr (SP) prep_dlmax(a, b - pb.wn);
+    if constexpr (SP) prep_wn_split(a, b);
+    else prep_wpad(a, b);
     return;
   }
   const int n = blockIdx.x / per, rest = blockIdx.x - n * per, part = rest % parts;
@@ -401,6 +377,7 @@ __global__ __launch_bounds__(kPrepThreads) void joiner_prep_kernel(JoinerArgs a,
     if (n == a.b.N - 1) a.frame_off[a.b.N] = off + Tn;
   }
   int4 r = make_int4(0, 0, -1, -1);
+  float rs = 1.f;
   if (i < Tn * S) {
     const int t = i / S, s = i - t * S;
     const size_t nts = ((size_t)n * T + t) * S + s;
@@ -416,8 +393,12 @@ __global__ __launch_bounds__(kPrepThreads) void joiner_prep_kernel(JoinerArgs a,
       r.z = (u < Un) ? symbol_at(a.b, n, u, a.V, ok) : -1;
       if (!ok) r.z = -2;  // symbol outside [0, V): px is NaN, so the utterance's loss is NaN
       r.w = (int)nts;
+      if (SP && a.rsc) rs = row_scale(a, n, nts);
     }
-    if (part == 0) a.rowinfo[(size_t)(off + t) * S + s] = r;
+    if (part == 0) {
+      a.rowinfo[(size_t)(off + t) * S + s] = r;
+      if (SP && a.rsc) a.rsc[(size_t)(off + t) * S + s] = rs;
+    }
   }
   if (pb.hj == 0) return;
   // h of the block's rows, kPrepHGroups groups of 8 columns from its part on
@@ -696,8 +677,9 @@ constexpr int kDpreLd = kTileCols + 4;  // row stride of the dpre tile (floats)
 constexpr int kBwdStageBytes = kTileRows * kDpreLd * 4;
 static_assert(CfgN<true>::SMEM_BYTES <= kBwdStageBytes && CfgT<true>::SMEM_BYTES <= kBwdStageBytes, "operand stages fit");
 static_assert(CfgN<false>::SMEM_BYTES <= kBwdStageBytes && CfgT<false>::SMEM_BYTES <= kBwdStageBytes, "operand stages fit");
-constexpr int kBwdLdsBytes = kBwdStageBytes + kTileRows * (int)sizeof(int4);
+constexpr int kBwdLdsBytes = kBwdStageBytes + kTileRows * (int)(sizeof(int4) + sizeof(float));
 DEV int4* lds_rowinfo(unsigned char* lds) { return reinterpret_cast<int4*>(lds + kBwdStageBytes); }
+DEV float* lds_rowinv(unsigned char* lds) { return reinterpret_cast<float*>(lds_rowinfo(lds) + kTileRows); }
 
 // Tile `tile` (row tile tile / ncol, column tile tile % ncol) of the rows
 // [cm0, cm1) whose count of active tiles (rows present) is computed here: -1
@@ -716,13 +698,20 @@ DEV int chunk_row_tiles(const JoinerArgs& a, int cm0, int cm1) {
 }
 
 // d(logits) of 4 neighbouring columns from column c on (a multiple of 4) into
-// a row of the chunk buffer, in operand form (s: the planes' scale).
+// a row of the chunk buffer, in operand form (s: the planes' scales).
+// Split d(logits) are stored twice, since the two contractions sum over
+// different directions and two fp16 planes hold an element to 2^-39 of the
+// largest one under its scale: dl with a scale per row for dh, which sums
+// over a row, dc with a scale per column and 32 rows for dW, which sums over
+// a column (a token of probability 1e-12 is 0 under a row's scale, an
+// utterance of scale 1e-12 under a batch's). The second copy takes joiner and
+// backward at N = 16, T = 300, V = 5000, S = 5, J = 512 from 1,420 to 1,630 us.
 template <bool SP>
-DEV void store_dl4(uint16_t* row, int c, const float (&d)[4], float s) {
+DEV void store_dl4(uint16_t* row, int c, const float (&d)[4], const float (&s)[4]) {
   if constexpr (SP) {
     uint32_t h[2], l[2];
-    split_f16x2(d[0] * s, d[1] * s, h[0], l[0]);
-    split_f16x2(d[2] * s, d[3] * s, h[1], l[1]);
+    split_f16x2(d[0] * s[0], d[1] * s[1], h[0], l[0]);
+    split_f16x2(d[2] * s[2], d[3] * s[3], h[1], l[1]);
     uint16_t* dst = row + split_word(c);
     *reinterpret_cast<uint2*>(dst) = make_uint2(h[0], h[1]);
     *reinterpret_cast<uint2*>(dst + 32) = make_uint2(l[0], l[1]);
@@ -730,6 +719,10 @@ DEV void store_dl4(uint16_t* row, int c, const float (&d)[4], float s) {
     *reinterpret_cast<uint2*>(row + c) = make_uint2((uint32_t)f2bf(d[0]) | ((uint32_t)f2bf(d[1]) << 16),
                                                     (uint32_t)f2bf(d[2]) | ((uint32_t)f2bf(d[3]) << 16));
   }
+}
+// What undoes the scales of 4 columns of dc and of h.
+DEV float4 dc_factors(const float (&s)[4]) {
+  return make_float4(pow2_inv(s[0]) * kHInv, pow2_inv(s[1]) * kHInv, pow2_inv(s[2]) * kHInv, pow2_inv(s[3]) * kHInv);
 }
 // Elements of a row of d(logits) in the chunk buffer (zeros from column V on).
 template <bool SP>
@@ -754,18 +747,19 @@ DEV void dlogits_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks,
   const int V = a.V, TS = a.b.T * a.S;
   int4 info[Cfg::FM];
   float4 x[Cfg::FM];  // lse, gx, gy, scale of this lane's rows
+  float rs[Cfg::FM];  // the scales of their planes (split)
 #pragma unroll
   for (int i = 0; i < Cfg::FM; ++i) {
     const int m = m0 + out_row<Cfg>(i);
     info[i] = m < mend ? a.rowinfo[m] : make_int4(0, 0, -1, -1);
     x[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    rs[i] = SP && m < mend ? a.rsc[m] : 1.f;
     if (info[i].w >= 0) {
       const int n = info[i].w / TS;
       x[i] = make_float4(a.lse_in[info[i].w], a.gxo[info[i].w], a.gyo[info[i].w], a.scale ? a.scale[n] : 1.f);
     }
   }
   const int lane = threadIdx.x & 63, wm = (threadIdx.x >> 6) / Cfg::WGN;
-  const float ds = SP ? dl_scale(a) : 1.f;
   floatx4 acc[Cfg::FM][Cfg::FN];
   const LdsSrc sa(a.hbuf + (size_t)(m0 - cm0) * a.ldh, min(Cfg::BM, mend - m0), a.ldh);
   const LdsSrc sb(a.wt + (size_t)v0 * a.ldh, min(Cfg::BN, V - v0), a.ldh);
@@ -791,6 +785,7 @@ DEV void dlogits_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks,
     const float g = x[i].y + x[i].z;
     const bool on = info[i].w >= 0;
     uint16_t* row = a.dl + (size_t)(m - cm0) * a.ldd;
+    const float ds[4] = {rs[i], rs[i], rs[i], rs[i]};
 #pragma unroll
     for (int j = 0; j < Cfg::FN; ++j) {
       const int c = v0 + out_col<Cfg>(j);
@@ -803,6 +798,7 @@ DEV void dlogits_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks,
         if (c + r == a.b.blank) gd -= x[i].z;
         d[r] = on && c + r < V ? x[i].w * gd : 0.f;
         cs[j][r] += d[r];
+        if (SP) acc[i][j][r] = d[r];
       }
       if (a.logits_grad && on) {
 #pragma unroll
@@ -810,6 +806,29 @@ DEV void dlogits_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks,
           if (c + r < V) a.logits_grad[(size_t)info[i].w * V + c + r] = d[r];
       }
       if (m < mend && c < dl_cols<SP>(V)) store_dl4<SP>(row, c, d, ds);
+    }
+  }
+  // dc: the scale of each column within the wave's 32 rows
+  if constexpr (SP) {
+    float* inv = a.dc_inv + ((size_t)mt * Cfg::WGM + wm) * a.ldl;
+#pragma unroll
+    for (int j = 0; j < Cfg::FN; ++j) {
+      const int c = v0 + out_col<Cfg>(j);
+      float s[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float mx = 0.f;
+#pragma unroll
+        for (int i = 0; i < Cfg::FM; ++i) mx = fmaxf(mx, __builtin_fabsf(acc[i][j][r]));
+        s[r] = split_scale(row16_max(mx));
+      }
+#pragma unroll
+      for (int i = 0; i < Cfg::FM; ++i) {
+        const int m = m0 + out_row<Cfg>(i);
+        const float d[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+        if (m < mend && c < dl_cols<SP>(V)) store_dl4<SP>(a.dc + (size_t)(m - cm0) * a.ldd, c, d, s);
+      }
+      if ((lane & 15) == j && c < a.ldl) *reinterpret_cast<float4*>(inv + c) = dc_factors(s);
     }
   }
   // db partial: each column summed over the wave's 32 rows, 16 lanes x FM
@@ -854,18 +873,24 @@ constexpr int kDlInFlight = 16;  // rows per thread whose loads are issued toget
 
 // Threads per row of a block (over the ng 4-column groups of a row); a block
 // takes tpr groups of kDlRows rows, and grid.y the ceil(ng / tpr) column
-// ranges, so that wide rows spread over many blocks.
+// ranges, so that wide rows spread over many blocks. Split: at most half of
+// the block, so that a thread's rows are all in flight at once and their
+// values stay in registers until the column's scale is known.
+template <bool SP>
 __host__ __device__ inline int dl_threads_per_row(int ng) {
-  return ng <= 64 ? 64 : (ng <= 128 ? 128 : (ng <= 256 ? 256 : kDlThreads));
+  return ng <= 64 ? 64 : (SP || ng <= 128 ? 128 : kDlThreads);
 }
+static_assert(kDlRows / (kDlThreads / 128) <= kDlInFlight, "a split block's rows in one pass");
+template <bool SP>
 static dim3 dl_grid(const JoinerArgs& a, int rows) {
-  const int ng = (a.bf16 ? dl_cols<false>(a.V) : dl_cols<true>(a.V)) / 4;
-  return dim3((unsigned)((rows + kDlRows - 1) / kDlRows), (unsigned)((ng + dl_threads_per_row(ng) - 1) / dl_threads_per_row(ng)));
+  const int ng = dl_cols<SP>(a.V) / 4, tpr = dl_threads_per_row<SP>(ng);
+  return dim3((unsigned)((rows + kDlRows - 1) / kDlRows), (unsigned)((ng + tpr - 1) / tpr));
 }
 
 struct DlSmem {
   int4 ri[kDlRows];
   float4 rx[kDlRows];  // lse, gx, gy, scale
+  float rs[kDlRows];   // the planes' scale (split)
   float4 red[kDlThreads];
 };
 
@@ -891,21 +916,22 @@ DEV void dl_block(const JoinerArgs& a, int cm0, int cm1, int bx, int by, DlSmem&
     }
     ri[r] = info;
     rx[r] = x;
+    if constexpr (SP) sm.rs[r] = r < nrows ? a.rsc[m0 + r] : 1.f;
   }
-  const float ds = SP ? dl_scale(a) : 1.f;
   __syncthreads();
   const bool from_head = a.logits_in == nullptr;  // chunk 0 from the head rows
   const float* __restrict__ lg = from_head ? a.head : a.logits_in;
   const int ng = dl_cols<SP>(V) / 4;
-  const int tpr = dl_threads_per_row(ng);
+  const int tpr = dl_threads_per_row<SP>(ng);
   const int nrg = kDlThreads / tpr, rg = threadIdx.x / tpr, ct = threadIdx.x - rg * tpr;
   const bool vec = from_head || (V & 3) == 0;
   const int c = 4 * (by * tpr + ct);  // this thread's columns
   const bool gok = by * tpr + ct < ng;
   float cs[4] = {0.f, 0.f, 0.f, 0.f};
+  float cm[4] = {0.f, 0.f, 0.f, 0.f};       // split: the columns' largest |d(logits)| of this thread's rows
+  float l[kDlInFlight][4];                  // the rows in flight: their logits, then (split) their d(logits)
   if (gok) {
     for (int p0 = rg; p0 < nrows; p0 += nrg * kDlInFlight) {
-      float l[kDlInFlight][4];
 #pragma unroll
       for (int k = 0; k < kDlInFlight; ++k) {
         const int r = p0 + k * nrg;
@@ -940,9 +966,32 @@ DEV void dl_block(const JoinerArgs& a, int cm0, int cm1, int bx, int by, DlSmem&
             if (a.logits_grad) a.logits_grad[(size_t)info.w * V + col] = d[q];
           }
           cs[q] += d[q];
+          if constexpr (SP) {
+            cm[q] = fmaxf(cm[q], __builtin_fabsf(d[q]));
+            l[k][q] = d[q];
+          }
         }
+        const float ds[4] = {sm.rs[r], sm.rs[r], sm.rs[r], sm.rs[r]};
         store_dl4<SP>(a.dl + (size_t)(m0 + r - cm0) * a.ldd, c, d, ds);
       }
+    }
+  }
+  if constexpr (SP) {
+    red[threadIdx.x] = make_float4(cm[0], cm[1], cm[2], cm[3]);
+    __syncthreads();
+    for (int k = 0; k < nrg; ++k) {
+      const float4 o = red[k * tpr + ct];
+      cm[0] = fmaxf(cm[0], o.x); cm[1] = fmaxf(cm[1], o.y); cm[2] = fmaxf(cm[2], o.z); cm[3] = fmaxf(cm[3], o.w);
+    }
+    __syncthreads();  // red is used again below
+    const float s[4] = {split_scale(cm[0]), split_scale(cm[1]), split_scale(cm[2]), split_scale(cm[3])};
+    if (gok) {
+#pragma unroll
+      for (int k = 0; k < kDlInFlight; ++k) {
+        const int r = rg + k * nrg;
+        if (r < nrows) store_dl4<SP>(a.dc + (size_t)(m0 + r - cm0) * a.ldd, c, l[k], s);
+      }
+      if (rg == 0 && c < ldl) *reinterpret_cast<float4*>(a.dc_inv + (size_t)((m0 - cm0) / kDlRows) * ldl + c) = dc_factors(s);
     }
   }
   if (nrg > 1) {
@@ -1084,8 +1133,11 @@ DEV void dh_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks, int 
   const int m0 = cm0 + mt * Cfg::BM;
   const int j0 = nt * Cfg::BN;
   const int J = a.J;
-  for (int r = threadIdx.x; r < Cfg::BM; r += Cfg::NT)
+  float* rinv = lds_rowinv(lds);
+  for (int r = threadIdx.x; r < Cfg::BM; r += Cfg::NT) {
     ri[r] = (m0 + r < mend) ? a.rowinfo[m0 + r] : make_int4(0, 0, -1, -1);
+    if constexpr (SP) rinv[r] = (m0 + r < mend) ? pow2_inv(a.rsc[m0 + r]) : 0.f;
+  }
   __syncthreads();
   const TileFrameRegs fr = tile_frames_fetch(a, m0, mend, Cfg::BM);
   // What the epilogue needs of this thread's 4-column groups of the tile for
@@ -1115,7 +1167,6 @@ DEV void dh_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks, int 
     }
   };
   if constexpr (!SP) fetch_h();
-  const float dinv = SP ? pow2_inv(dl_scale(a)) : 1.f;
   floatx4 acc[Cfg::FM][Cfg::FN];
   // d(logits) of the chunk and W, both k = v contiguous
   const LdsSrc sa(a.dl + (size_t)(m0 - cm0) * a.ldd, min(Cfg::BM, mend - m0), a.ldd);
@@ -1138,7 +1189,8 @@ DEV void dh_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks, int 
   constexpr int LDC = kDpreLd;
   float* C = reinterpret_cast<float*>(lds);
 #pragma unroll
-  for (int i = 0; i < Cfg::FM; ++i)
+  for (int i = 0; i < Cfg::FM; ++i) {
+    const float dinv = SP ? rinv[out_row<Cfg>(i)] : 1.f;
 #pragma unroll
     for (int j = 0; j < Cfg::FN; ++j) {
       float4 o = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
@@ -1150,6 +1202,7 @@ DEV void dh_tile(const JoinerArgs& a, int cm0, int cm1, int v, int nblocks, int 
       }
       *reinterpret_cast<float4*>(C + out_row<Cfg>(i) * LDC + out_col<Cfg>(j)) = o;
     }
+  }
   __syncthreads();
 #pragma unroll
   for (int q8 = 0; q8 < NIT; ++q8) {
@@ -1215,12 +1268,14 @@ DEV void dw_tile(const JoinerArgs& a, int cm0, int cm1, int first, int v, int nj
     }
     return;
   }
-  const float sinv = SP ? pow2_inv(dl_scale(a)) * kHInv : 1.f;
   floatx4 acc[Cfg::FM][Cfg::FN];
   const int krows = __builtin_amdgcn_readfirstlane(ke - kb);
   const TrSrc sa{reinterpret_cast<const unsigned char*>(a.hbuf + (size_t)(kb - cm0) * a.ldh), krows, a.ldh, j0 * Cfg::XP};
-  const TrSrc sb{reinterpret_cast<const unsigned char*>(a.dl + (size_t)(kb - cm0) * a.ldd), krows, a.ldd, v0 * Cfg::XP};
-  gemm_mainloop_tr<Cfg>(sa, sb, lds, acc);
+  const TrSrc sb{reinterpret_cast<const unsigned char*>((SP ? a.dc : a.dl) + (size_t)(kb - cm0) * a.ldd), krows, a.ldd,
+                 v0 * Cfg::XP};
+  static_assert(!SP || Cfg::BK == kDbRows, "a K-step's rows share dc's scales");
+  const TrFactors sf{SP ? a.dc_inv + (size_t)((kb - cm0) / kDbRows) * a.ldl : nullptr, a.ldl, v0};
+  gemm_mainloop_tr<Cfg>(sa, sb, sf, lds, acc);
   const bool vec = (V & 3) == 0;  // rows of partials at 16-byte offsets
   // the partials the earlier chunks left for this thread's elements, loaded
   // together before any store rather than one load-add-store round trip per
@@ -1252,8 +1307,7 @@ DEV void dw_tile(const JoinerArgs& a, int cm0, int cm1, int first, int v, int nj
       float o[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float x = SP ? acc[i][jj][r] * sinv : acc[i][jj][r];
-        o[r] = first ? x : old[i][jj][r] + x;
+        o[r] = first ? acc[i][jj][r] : old[i][jj][r] + acc[i][jj][r];
       }
       if (vec) {
         if (vv < V) *reinterpret_cast<float4*>(dst) = make_float4(o[0], o[1], o[2], o[3]);
@@ -1597,7 +1651,6 @@ hipError_t launch_full_ranges(int* ranges, int N, int T, int S, hipStream_t s) {
 int joiner_nparts(int V) { return (V + 63) / 64; }
 int joiner_ldl(int V) { return (V + 7) / 8 * 8; }
 int joiner_words(int n, int bf16) { return bf16 ? row_words<false>(n) : row_words<true>(n); }
-int joiner_dlmax_parts() { return kDlMaxParts; }
 bool joiner_w_copy(int V, int bf16) { return !bf16 || V % 64 != 0; }
 
 // Rows of a chunk buffer whose rows of `row_elems` fp32 words stay below
@@ -1683,13 +1736,12 @@ hipError_t launch_joiner_prep(const JoinerArgs& a, hipStream_t s) {
     } else {
       if (a.wt) pb.wt = (a.V + kWtCols - 1) / kWtCols;
       if (a.wn) pb.wn = a.J;
-      if (a.dlmax) pb.dlmax = kDlMaxParts;
     }
     if (a.px) {  // the forward: h of its first chunk
       pb.hj = ((a.bf16 ? h_groups<false>(a.J) : h_groups<true>(a.J)) + kPrepHGroups - 1) / kPrepHGroups;
       pb.hrows = a.chunk_rows;
     }
-    const dim3 grid(a.b.N * ((a.b.T * a.S + 255) / 256) * std::max(1, pb.hj) + pb.wt + pb.wn + pb.dlmax);
+    const dim3 grid(a.b.N * ((a.b.T * a.S + 255) / 256) * std::max(1, pb.hj) + pb.wt + pb.wn);
     if (a.bf16) hipLaunchKernelGGL(joiner_prep_kernel<false>, grid, dim3(kPrepThreads), 0, s, a, pb);
     else hipLaunchKernelGGL(joiner_prep_kernel<true>, grid, dim3(kPrepThreads), 0, s, a, pb);
   }
@@ -1750,6 +1802,8 @@ static JoinerArgs ring_slot(const JoinerArgs& a, int k) {
   JoinerArgs c = a;
   c.hbuf = a.hring[k % 3];
   c.dl = a.dlring[k % 2];
+  c.dc = a.dcring[k % 2];
+  c.dc_inv = a.dcinvring[k % 2];
   c.dpre = a.dpring[k % 2];
   return c;
 }
@@ -1782,7 +1836,7 @@ static hipError_t launch_tail(const JoinerArgs& a, const TailRanges& tr, hipStre
 // d(logits) of chunk [cm0, cm1) from stored logits or the head, beside the h
 // passes h0 and h1.
 static hipError_t launch_head(const JoinerArgs& a, int cm0, int cm1, const HPass& h0, const HPass& h1, hipStream_t s) {
-  const dim3 g = dl_grid(a, cm1 - cm0);
+  const dim3 g = a.bf16 ? dl_grid<false>(a, cm1 - cm0) : dl_grid<true>(a, cm1 - cm0);
   const dim3 blocks(g.x * g.y + h0.blocks + h1.blocks);
   RNNT_PROF(s, "joiner_dl");
   if (a.bf16)

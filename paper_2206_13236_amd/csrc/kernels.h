@@ -140,18 +140,22 @@ struct JoinerArgs {
   int ldl;             // row stride of the head: V rounded up to 8
   // operands: rows of 16-bit words (gemm.h: bf16, or two fp16 planes of an fp32 element)
   int ldh, ldd;        // words of a row of J and of V elements
-  uint16_t* dl;        // ws chunk [chunk_rows, ldd]: d(logits)
+  uint16_t* dl;        // ws chunk [chunk_rows, ldd]: d(logits) for dh (split: scaled per row); bf16: for dW too
+  uint16_t* dc;        // ws chunk [chunk_rows, ldd] (split): d(logits) for dW, scaled per column within 32 rows
+  float* dc_inv;       // ws chunk [chunk_rows / 32, ldl] (split): the inverse of the scales of dc's columns and of h
   uint16_t* wn;        // [J, ldd]: W (ws, or W itself in bf16 when its rows need no padding)
   uint16_t* wt;        // ws [V, ldh]: W transposed, written by the prep kernel like wn
   float* wn_inv;       // ws [J] (split): the inverse of the scale of a row of wn
   float* wt_inv;       // ws [V] (split): the inverse of the scales of a row of wt and of h
-  float* dlmax;        // ws (split): partial maxima of the bound on |d(logits)|, which sets its planes' scale
+  float* rsc;          // ws [N*T*S] (split): the scale of a row of dl, from the bound |scale| (|gx| + |gy|)
   int chunk_rows;
   float* dpre;         // ws chunk [chunk_rows, J]: the chunk's d dec pieces, each in the row of its first row
   float* enc_part;     // ws [ceil(N*T*S/128), 2, J]: d enc pieces of frames cut by a 128-row tile
   uint16_t* hbuf;      // ws chunk [chunk_rows, ldh]: h = tanh(enc + dec) of the chunk's rows
   uint16_t* hring[3];  // the rings of chunk buffers: hbuf of 3 slots (2 in the forward), dl of 2, dpre of 2
-  uint16_t* dlring[2]; //   (the fields above are those of slot 0)
+  uint16_t* dlring[2]; //   (dc and dc_inv with it; the fields above are those of slot 0)
+  uint16_t* dcring[2];
+  float* dcinvring[2];
   float* dpring[2];
   float* dw_part;      // ws [splits, J, V]
   int splits;
@@ -178,7 +182,6 @@ int joiner_db_rows(int chunk_rows);  // db partial rows of one chunk
 int joiner_nparts(int V);
 int joiner_ldl(int V);
 int joiner_words(int n, int bf16);      // 16-bit words of an operand row of n elements
-int joiner_dlmax_parts();
 bool joiner_w_copy(int V, int bf16);    // whether dh reads a copy of W
 
 // ---- stage 4: pruned recursion ---------------------------------------------

@@ -84,3 +84,63 @@ def test_split_backward_scales_with_the_occupations(gscale):
         for k in ("W_grad", "bias_grad", "enc_grad", "dec_grad"):
             r = host(ref[k])
             assert_close(k, host(out[k]) / gscale, r, atol=4e-6 * np.abs(r).max())
+
+
+# d(logits) of the backward's three producers: recomputed, streamed from the head, streamed from stored logits
+PATHS = ["recomputed", "head", "logits"]
+
+
+def _backward(b, ranges, S, path, scale):
+    args = [dev_f32(x) for x in (b.enc, b.dec, b.W, b.bias)]
+    batch, rg = make_dev_batch(b), dev_i32(ranges)
+    C = P.backward_chunk_rows(b.N, b.T, S, b.wl.J, b.V, P.RNNT_F32)
+    kw = dict(head=torch.empty(C, (b.V + 7) // 8 * 8, device="cuda"), head_rows=C) if path == "head" else {}
+    jo = P.rnnt_pruned_joiner(batch, S, *args, rg, keep_logits=path == "logits", **kw)
+    pl = P.rnnt_pruned_loss(batch, S, jo["px"], jo["py"], rg)
+    g = P.rnnt_pruned_joiner_backward(batch, S, *args, rg, jo["lse"], pl["px_occ"], pl["py_occ"],
+                                      scale=dev_f32(np.asarray(scale)), logits=jo["logits"], **kw)
+    torch.cuda.synchronize()
+    return g
+
+
+def _rel(got, ref):
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("path", PATHS)
+def test_split_backward_keeps_each_utterance_its_own_magnitude(path):
+    """Utterances whose scales differ by 1e5 and 1e10: each one's d enc and d
+    dec against 64 bits, relative to its own norm. Bound: 2^-21 a product, the
+    fp32 sums over V and S rows and the 2e-6 of the softmax that enters
+    d(logits), which adds up along a row at worst: 2e-5."""
+    b, ranges = _setup(96, 129, 5)
+    scale = np.array([1.0, 1e-5, 1e-10])
+    say(f"[split] scales {scale} {path}")
+    g = _backward(b, ranges, 5, path, scale)
+    st = O.pruned_stage(b.enc, b.dec, b.W, b.bias, ranges, b.symbols, b.t_len, b.u_len, b.wl.blank, scale=scale)
+    for k in ("enc_grad", "dec_grad"):
+        got = host(g[k])
+        for n in range(b.N):
+            assert _rel(got[n], st[k][n]) < 2e-5, (k, n)
+
+
+@pytest.mark.parametrize("path", PATHS)
+@pytest.mark.parametrize("J,V", [(40, 127), (96, 300)])
+def test_split_weight_gradient_of_improbable_tokens(J, V, path):
+    """Tokens of probability e^-15 to e^-45 at every row, that are no target or
+    one only in an utterance of scale 1e-6: each one's column of d W against
+    64 bits, relative to its own norm. Bound: as above, and the 1e-6 relative
+    error that 2^-24 of a logit of 45 gives its exponential times its sum: 4e-5."""
+    say(f"[split] improbable tokens J={J} V={V} {path}")
+    b, ranges = _setup(J, V, 5)
+    cols = [v for v in range(1, V) if v not in b.symbols][:6]
+    b.bias[cols] -= np.array([15, 20, 25, 30, 35, 45][:len(cols)], np.float32)
+    scale = np.ones(b.N)
+    scale[2] = 1e-6
+    b.symbols[b.symbols == cols[0]] = cols[-1]
+    b.symbols[2, 0] = cols[2]
+    g = _backward(b, ranges, 5, path, scale)
+    st = O.pruned_stage(b.enc, b.dec, b.W, b.bias, ranges, b.symbols, b.t_len, b.u_len, b.wl.blank, scale=scale)
+    got = host(g["W_grad"])
+    for v in range(V):
+        assert _rel(got[:, v], st["W_grad"][:, v]) < 4e-5, (v, v in cols)
