@@ -273,12 +273,13 @@ constexpr __host__ __device__ int row_words(int n) { return SPLIT ? (n + 31) / 3
 // Word of element k's hi plane within its row (its lo plane: 32 words on).
 DEV int split_word(int k) { return (k >> 5) * 64 + (k & 31); }
 
-// The planes of an (already scaled) element. A value beyond fp16 or a NaN
-// keeps a zero lo plane, so that it meets the product as itself once.
+// The planes of an (already scaled) element. A value beyond fp16 (infinity) or
+// a NaN is the lo plane, beside a zero hi plane: of the other operand it meets
+// the hi plane alone, whose sign is the element's (its lo plane may have the
+// other sign, or be zero), so that a product with infinity is what it is in fp32.
 DEV void split_f16(float x, uint16_t& hi, uint16_t& lo) {
-  const _Float16 h = (_Float16)x;
-  const float r = x - (float)h;
-  const _Float16 l = (_Float16)(__builtin_fabsf(r) <= 65504.f ? r : 0.f);
+  const _Float16 h = (_Float16)(__builtin_fabsf(x) < 65520.f ? x : 0.f);
+  const _Float16 l = (_Float16)(x - (float)h);
   hi = __builtin_bit_cast(uint16_t, h);
   lo = __builtin_bit_cast(uint16_t, l);
 }

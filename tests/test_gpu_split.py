@@ -144,3 +144,30 @@ def test_split_weight_gradient_of_improbable_tokens(J, V, path):
     got = host(g["W_grad"])
     for v in range(V):
         assert _rel(got[:, v], st["W_grad"][:, v]) < 4e-5, (v, v in cols)
+
+
+@pytest.mark.parametrize("J,V", [(40, 127), (64, 2100)])
+def test_split_forward_with_an_infinite_weight(J, V):
+    """W = -inf where h > 0 at every row masks a token: its logit is -inf, the
+    others and the loss are those of 64 bits. A NaN makes the logits of its
+    column NaN and no others. (rtol and atol as for finite W.)"""
+    say(f"[split] infinite weight J={J} V={V}")
+    b, ranges = _setup(J, V, 5)
+    v0 = next(v for v in range(1, V) if v not in b.symbols)
+    b.enc[..., 3] = np.abs(b.enc[..., 3])
+    b.dec[..., 3] = np.abs(b.dec[..., 3])
+    b.W[3, v0] = -np.inf
+    jo, pl, _ = _run(b, ranges, 5)
+    with np.errstate(invalid="ignore"):
+        px, py, lse = O.pruned_joiner_logprobs(b.enc, b.dec, b.W, b.bias, ranges, b.symbols, b.t_len, b.u_len, 0)
+    loss, _, _ = O.pruned_loss(px, py, ranges, b.t_len, b.u_len)
+    assert np.isfinite(loss).all()
+    assert_close("lse", host(jo["lse"]), lse, atol=5e-5)
+    assert_close("px", host(jo["px"]), px, atol=5e-5)
+    assert_close("pruned_loss", host(pl["loss"]), loss, rtol=1e-5)
+    b.W[3, v0] = np.nan
+    jo, pl, _ = _run(b, ranges, 5)
+    on = np.arange(b.T)[None, :, None] < b.t_len[:, None, None]
+    on = on & (ranges <= b.u_len[:, None, None])
+    nan = np.isnan(host(jo["logits"])[on])
+    assert nan[:, v0].all() and nan.sum() == on.sum() and np.isnan(host(pl["loss"])).all()
