@@ -192,6 +192,13 @@ size_t rnnt_pruned_joiner_workspace_size(int32_t N, int32_t T, int32_t S, int32_
  *
  * enc [N, T, J], dec [N, U+1, J], W [J, V], bias [V] (nullable = 0): dtype
  *   RNNT_F32 (float) or RNNT_BF16 (bfloat16 bits); accumulation is fp32.
+ *   RNNT_F32 contracts two fp16 planes per element: an element enters to an
+ *   fp32 ulp of itself where it is at least 2^-16 of the largest element of its
+ *   row or column of W (h: of 1), and to 2^-38 of that largest one below. So an
+ *   entry of W more than 2^17 times the rest of its row or column costs those
+ *   precision. d(logits) in the backward: to 2^-38 of its row's
+ *   |scale| (px_occ + py_occ) in d enc and d dec, and of the largest element of
+ *   its column among 32 rows in d W.
  * ranges [N, T, S] int32 from rnnt_prune_ranges (u values above u_len[n] mark
  *   absent slots).
  * Outputs, fp32 [N, T, S]: px = logits[y_{u+1}] - lse (u < U_n, else -inf),
