@@ -588,6 +588,18 @@ def _scaled_gradients(g, divisor: float, saved, dtypes, has_bias: bool):
     return grads if has_bias else grads[:5] + [None]
 
 
+def _readable(t: torch.Tensor) -> bool:
+    """Whether a kernel can read t through its address and nothing of it is lost by that: a plain CUDA tensor, no
+    subclass, no vmap or functorch wrapper (which have no storage) and no forward-mode dual."""
+    if type(t) is not torch.Tensor or not t.is_cuda or torch.autograd.forward_ad.unpack_dual(t).tangent is not None:
+        return False
+    try:
+        t.data_ptr()
+    except RuntimeError:
+        return False
+    return True
+
+
 class _PrunedRnntFunction(torch.autograd.Function):
     """Forward computes the loss and every gradient at once (the kernels are
     fused forward-backward); backward scales the stored gradients."""
@@ -614,7 +626,8 @@ class _PrunedRnntFunction(torch.autograd.Function):
     def backward(ctx, g):
         saved = ctx.saved_tensors
         # (a saved-tensor hook may have replaced the stored arrays)
-        plain = all(t.is_cuda and t.dtype == torch.float32 and t.is_contiguous() for t in saved) and g.is_cuda
+        plain = _readable(g) and all(_readable(t) and t.device == g.device and t.dtype == torch.float32 and
+                                    t.is_contiguous() for t in saved)
         if plain and not (torch.is_grad_enabled() and g.requires_grad):
             return (*_scaled_gradients(g, float(ctx.N) if ctx.reduction == "mean" else 1.0, saved, ctx.dtypes,
                                        ctx.has_bias), None, None, None)

@@ -94,3 +94,26 @@ def test_backward_through_hooks_and_create_graph():
     for r, a, f in zip(ref, got, first):
         assert torch.equal(a, r) and torch.allclose(f, 2 * r, rtol=1e-6)
     assert torch.allclose(dw, ref[0].sum(), rtol=1e-4, atol=1e-5)
+
+
+def test_backward_of_batched_and_dual_gradients():
+    """Incoming gradients that are no plain arrays take torch's own products: a batch of them (vmap has no storage
+    to point at) and a forward-mode dual (whose tangent is the gradients' tangent)."""
+    b = make_batch("tiny")
+    batch = make_dev_batch(b)
+    leaves = [t.requires_grad_(True) for t in (dev_f32(b.am), dev_f32(b.lm), *(dev_joiner(x, False) for x in
+                                                                               (b.enc, b.dec, b.W, b.bias)))]
+    loss = P.pruned_rnnt_loss(*leaves, batch, b.wl.S, reduction="mean")
+    ref = torch.autograd.grad(loss, leaves, retain_graph=True)
+    gs = torch.tensor([1.0, -0.5, 3.0], device="cuda")
+    got = torch.autograd.grad(loss, leaves, gs, is_grads_batched=True, retain_graph=True)
+    for r, x in zip(ref, got):
+        assert x.shape == (3, *r.shape)
+        for k, f in enumerate(gs.tolist()):
+            assert torch.allclose(x[k], f * r, rtol=1e-6, atol=0)
+    with torch.autograd.forward_ad.dual_level():
+        g = torch.autograd.forward_ad.make_dual(torch.ones((), device="cuda"), torch.full((), 0.25, device="cuda"))
+        got = torch.autograd.grad(loss, leaves, g)
+        for r, x in zip(ref, got):
+            v, t = torch.autograd.forward_ad.unpack_dual(x)
+            assert torch.allclose(v, r, rtol=1e-6, atol=0) and torch.allclose(t, 0.25 * r, rtol=1e-6, atol=0)
