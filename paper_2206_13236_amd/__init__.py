@@ -10,6 +10,7 @@ step does (Sec. 3.3: loss = pruned + 0.5 * simple).
 from __future__ import annotations
 
 import ctypes
+import math
 from typing import Optional
 
 import torch
@@ -52,6 +53,21 @@ def _need(t: torch.Tensor, name: str, dtype: torch.dtype, shape: tuple):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
+
+
+def _array(t: Optional[torch.Tensor], name: str, dtype: torch.dtype, *shape: int):
+    """A caller's array that a kernel reads or writes densely: None, or contiguous device memory that holds the shape
+    (in any shape of its own)."""
+    if t is None:
+        return
+    if not isinstance(t, torch.Tensor):
+        raise TypeError(f"{name} must be a tensor")
+    if t.device.type != "cuda":
+        raise ValueError(f"{name} must be a device (cuda) tensor")
+    if t.dtype != dtype:
+        raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
+    if not t.is_contiguous() or t.numel() < math.prod(shape):
+        raise ValueError(f"{name} must be contiguous with at least the elements of {shape}, got {tuple(t.shape)}")
 
 
 def _ws(nbytes: int, device, workspace: Optional[torch.Tensor]) -> torch.Tensor:
@@ -131,6 +147,11 @@ def rnnt_simple_loss(batch: Batch, V: int, am: torch.Tensor, lm: torch.Tensor,
     dev = batch.device
     _need(am, "am", torch.float32, (N, T, V))
     _need(lm, "lm", torch.float32, (N, U + 1, V))
+    _array(loss, "loss", torch.float32, N)
+    for name, t in (("px_occ", px_occ), ("py_occ", py_occ), ("px", px), ("py", py)):
+        _array(t, name, torch.float32, N, T, U + 1)
+    _array(am_grad, "am_grad", torch.float32, N, T, V)
+    _array(lm_grad, "lm_grad", torch.float32, N, U + 1, V)
     f32 = dict(dtype=torch.float32, device=dev)
     loss = torch.empty(N, **f32) if loss is None else loss
     px_occ = torch.empty(N, T, U + 1, **f32) if px_occ is None else px_occ
@@ -160,6 +181,8 @@ def rnnt_simple_loss_backward(batch: Batch, V: int, am: torch.Tensor, lm: torch.
     _need(am, "am", torch.float32, (N, T, V))
     _need(lm, "lm", torch.float32, (N, U + 1, V))
     _need(px_occ, "px_occ", torch.float32, (N, T, U + 1))
+    _array(am_grad, "am_grad", torch.float32, N, T, V)
+    _array(lm_grad, "lm_grad", torch.float32, N, U + 1, V)
     if scale is not None:
         _need(scale, "scale", torch.float32, (N,))
     f32 = dict(dtype=torch.float32, device=dev)
@@ -177,6 +200,7 @@ def rnnt_prune_ranges(batch: Batch, S: int, px_occ: torch.Tensor, py_occ: torch.
     N, T, U = batch.N, batch.T, batch.U
     _need(px_occ, "px_occ", torch.float32, (N, T, U + 1))
     _need(py_occ, "py_occ", torch.float32, (N, T, U + 1))
+    _array(ranges, "ranges", torch.int32, N, T, S)
     ranges = torch.empty(N, T, S, dtype=torch.int32, device=batch.device) if ranges is None else ranges
     check(lib().rnnt_prune_ranges(batch.c, S, _p(px_occ), _p(py_occ), _p(ranges), _stream(stream)))
     return ranges
@@ -198,9 +222,12 @@ def rnnt_pruned_joiner(batch: Batch, S: int, enc: torch.Tensor, dec: torch.Tenso
     dt = _jdtype(W)
     _need(enc, "enc", W.dtype, (N, T, J))
     _need(dec, "dec", W.dtype, (N, U + 1, J))
+    _need(W, "W", W.dtype, (J, V))
     if bias is not None:
         _need(bias, "bias", W.dtype, (V,))
     _need(ranges, "ranges", torch.int32, (N, T, S))
+    for name, t in (("px", px), ("py", py), ("lse", lse)):
+        _array(t, name, torch.float32, N, T, S)
     f32 = dict(dtype=torch.float32, device=batch.device)
     px = torch.empty(N, T, S, **f32) if px is None else px
     py = torch.empty(N, T, S, **f32) if py is None else py
@@ -234,6 +261,9 @@ def rnnt_pruned_loss(batch: Batch, S: int, px: torch.Tensor, py: torch.Tensor, r
     _need(px, "px", torch.float32, (N, T, S))
     _need(py, "py", torch.float32, (N, T, S))
     _need(ranges, "ranges", torch.int32, (N, T, S))
+    _array(loss, "loss", torch.float32, N)
+    _array(px_occ, "px_occ", torch.float32, N, T, S)
+    _array(py_occ, "py_occ", torch.float32, N, T, S)
     f32 = dict(dtype=torch.float32, device=batch.device)
     loss = torch.empty(N, **f32) if loss is None else loss
     if want_occupations and px_occ is None:
@@ -257,6 +287,9 @@ def rnnt_pruned_loss_noalloc(batch: Batch, S: int, px: torch.Tensor, py: torch.T
     _need(px, "px", torch.float32, (N, T, S))
     _need(py, "py", torch.float32, (N, T, S))
     _need(ranges, "ranges", torch.int32, (N, T, S))
+    _array(loss, "loss", torch.float32, N)
+    _array(px_occ, "px_occ", torch.float32, N, T, S)
+    _array(py_occ, "py_occ", torch.float32, N, T, S)
     f32 = dict(dtype=torch.float32, device=batch.device)
     loss = torch.empty(N, **f32) if loss is None else loss
     check(lib().rnnt_pruned_loss_noalloc(batch.c, S, _p(px), _p(py), _p(ranges), _p(loss), _p(px_occ), _p(py_occ),
@@ -277,6 +310,13 @@ def rnnt_pruned_joiner_backward(batch: Batch, S: int, enc, dec, W, bias, ranges,
     dt = _jdtype(W)
     _need(enc, "enc", W.dtype, (N, T, J))
     _need(dec, "dec", W.dtype, (N, U + 1, J))
+    _need(W, "W", W.dtype, (J, V))
+    _array(bias, "bias", W.dtype, V)
+    _array(scale, "scale", torch.float32, N)
+    for name, t, *shape in (("enc_grad", enc_grad, N, T, J), ("dec_grad", dec_grad, N, U + 1, J),
+                            ("W_grad", W_grad, J, V), ("bias_grad", bias_grad, V),
+                            ("logits_grad", logits_grad, N, T, S, V)):
+        _array(t, name, torch.float32, *shape)
     for name, t in (("lse", lse), ("px_occ", px_occ), ("py_occ", py_occ)):
         _need(t, name, torch.float32, (N, T, S))
     _need(ranges, "ranges", torch.int32, (N, T, S))
@@ -316,6 +356,8 @@ def rnnt_combine_losses(simple_loss: Optional[torch.Tensor], pruned_loss: Option
     for name, t in (("simple_loss", simple_loss), ("pruned_loss", pruned_loss)):
         if t is not None:
             _need(t, name, torch.float32, (N,))
+    _array(loss, "loss", torch.float32, N)
+    _array(total, "total", torch.float32)
     f32 = dict(dtype=torch.float32, device=ref.device)
     loss = torch.empty(N, **f32) if loss is None else loss
     total = torch.empty((), **f32) if total is None else total
@@ -342,6 +384,7 @@ def rnnt_validate_inputs(batch: Batch, V: int, S: int = 0, am=None, lm=None, enc
             _need(enc, "enc", ref.dtype, (N, T, J))
         if dec is not None:
             _need(dec, "dec", ref.dtype, (N, U + 1, J))
+    _array(flags, "flags", torch.int32, N)
     flags = torch.empty(N, dtype=torch.int32, device=batch.device) if flags is None else flags
     n_bad = ctypes.c_int32(0)
     check(lib().rnnt_validate_inputs(batch.c, V, S, J, dt, _p(am), _p(lm), _p(enc), _p(dec), _p(flags),
@@ -364,10 +407,14 @@ def rnnt_full_loss(batch: Batch, enc, dec, W, bias=None, scale=None, keep_logits
     dt = _jdtype(W)
     _need(enc, "enc", W.dtype, (N, T, J))
     _need(dec, "dec", W.dtype, (N, U + 1, J))
+    _need(W, "W", W.dtype, (J, V))
     if bias is not None:
         _need(bias, "bias", W.dtype, (V,))
     if scale is not None:
         _need(scale, "scale", torch.float32, (N,))
+    for name, t, *shape in (("loss", loss, N), ("enc_grad", enc_grad, N, T, J), ("dec_grad", dec_grad, N, U + 1, J),
+                            ("W_grad", W_grad, J, V), ("bias_grad", bias_grad, V), ("logits", logits, N, T, U + 1, V)):
+        _array(t, name, torch.float32, *shape)
     f32 = dict(dtype=torch.float32, device=batch.device)
     loss = torch.empty(N, **f32) if loss is None else loss
     enc_grad = torch.empty(N, T, J, **f32) if enc_grad is None else enc_grad
@@ -532,20 +579,23 @@ class PrunedRnntLoss:
 
         _need(enc, "enc", W.dtype, (N, T, J))
         _need(dec, "dec", W.dtype, (N, U + 1, J))
-        if int(W.shape[1]) != V:
-            raise ValueError(f"W must have shape {(J, V)}, got {tuple(W.shape)}")
+        _need(W, "W", W.dtype, (J, V))
         if bias is not None:
             _need(bias, "bias", W.dtype, (V,))
         res.update(pruned_loss=o("pruned_loss", (N,)), ranges=o("ranges", band, torch.int32), px=o("px", band),
                    py=o("py", band), lse=o("lse", band), pruned_px_occ=o("pruned_px_occ", band),
                    pruned_py_occ=o("pruned_py_occ", band), loss=o("loss", (N,)), total=o("total", ()))
         logits = o("logits", (N, T, S, V)) if self.keep_logits else None
-        for key in out:  # arrays that a later stage reads back
-            shape = {"simple_loss": (N,), "pruned_loss": (N,), "simple_px_occ": lat, "simple_py_occ": lat, "ranges": band,
-                     "px": band, "py": band, "lse": band, "pruned_px_occ": band, "pruned_py_occ": band,
-                     "logits": (N, T, S, V)}.get(key)
-            if shape is not None and out[key] is not None and (key != "logits" or logits is not None):
-                _need(out[key], key, torch.int32 if key == "ranges" else f32, shape)
+        # arrays that a later stage reads back have their shape, the others room for what is written
+        back = {"simple_loss": (N,), "pruned_loss": (N,), "simple_px_occ": lat, "simple_py_occ": lat, "ranges": band,
+                "px": band, "py": band, "lse": band, "pruned_px_occ": band, "pruned_py_occ": band, "logits": (N, T, S, V)}
+        written = {"am_grad": (N, T, V), "lm_grad": (N, U + 1, V), "enc_grad": (N, T, J), "dec_grad": (N, U + 1, J),
+                   "W_grad": (J, V), "bias_grad": (V,), "loss": (N,), "total": ()}
+        for key, t in out.items():
+            if key in written:
+                _array(t, key, f32, *written[key])
+            elif key in back and t is not None and (key != "logits" or logits is not None):
+                _need(t, key, torch.int32 if key == "ranges" else f32, back[key])
         head = self._buf("head", (head_rows, (V + 7) // 8 * 8), f32, dev) if head_rows else None
         # the second stream's events cost more than what it would overlap on small batches
         overlap = self.overlap and N * T * (U + 1) * V >= _OVERLAP_WORK

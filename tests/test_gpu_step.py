@@ -60,6 +60,47 @@ def test_step_refuses_mismatched_arguments():
             step.step(batch, *bad)
     with pytest.raises(ValueError):
         step.step(batch, *args, out={"px": torch.empty(1, device="cuda")})
+    # W with the right shape but another layout (a linear layer's transposed weight) or in host memory
+    W = args[4]
+    for bad in (W.t().contiguous().t(), W.cpu()):
+        with pytest.raises(ValueError):
+            step.step(batch, *args[:4], bad, args[5])
+        with pytest.raises(ValueError):
+            P.rnnt_full_loss(batch, args[2], args[3], bad, args[5])
+        r = P.rnnt_prune_ranges(batch, b.wl.S, *(torch.rand(b.N, b.T, b.U + 1, device="cuda") for _ in range(2)))
+        with pytest.raises(ValueError):
+            P.rnnt_pruned_joiner(batch, b.wl.S, args[2], args[3], bad, args[5], r)
+        one = torch.zeros(b.N, b.T, b.wl.S, device="cuda")
+        with pytest.raises(ValueError):
+            P.rnnt_pruned_joiner_backward(batch, b.wl.S, args[2], args[3], bad, args[5], r, one, one, one)
+
+
+OUTPUTS = ["am_grad", "lm_grad", "enc_grad", "dec_grad", "W_grad", "bias_grad", "loss", "simple_loss", "pruned_loss"]
+
+
+@pytest.mark.parametrize("pruned_scale", [1.0, 0.0])
+def test_step_refuses_outputs_that_do_not_fit(pruned_scale):
+    """An output array too short, of another type, strided or in host memory is refused before anything is launched;
+    one of the right size in another shape is written."""
+    b = make_batch("tiny")
+    args = [dev_f32(b.am), dev_f32(b.lm), *(dev_joiner(x, False) for x in (b.enc, b.dec, b.W, b.bias))]
+    batch = make_dev_batch(b)
+    step = P.PrunedRnntLoss(b.wl.S, pruned_scale=pruned_scale)
+    ref = {k: v.clone() for k, v in step.step(batch, *args).items()}
+    for key in OUTPUTS:
+        good = torch.empty_like(ref[key])
+        bad = [good.flatten()[:-1].clone(), good.double(), good.cpu(),
+               torch.empty(2 * good.numel(), device="cuda")[::2].view_as(good)]
+        if pruned_scale == 0.0 and key in ("enc_grad", "dec_grad", "W_grad", "bias_grad", "pruned_loss"):
+            continue  # zeroed by torch, in whatever form
+        for t in bad:
+            with pytest.raises((ValueError, TypeError)):
+                step.step(batch, *args, out={key: t})
+    flat = {k: torch.empty(ref[k].numel(), device="cuda") for k in ("am_grad", "W_grad", "total")}
+    out = step.step(batch, *args, out=flat)
+    torch.cuda.synchronize()
+    for k, t in flat.items():
+        assert out[k] is t and torch.equal(t.view(ref[k].shape), ref[k]), k
 
 
 @pytest.mark.parametrize("divisor", [1.0, 13.0])
