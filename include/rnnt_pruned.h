@@ -415,7 +415,8 @@ int rnnt_train_step(const rnnt_batch* batch, const rnnt_step* step, void* stream
 /* dst = src * (factor[0] * (1 / divisor)) for up to RNNT_MAX_SCALED arrays in one
  * launch: stored gradients times an incoming one. factor [1] fp32 device;
  * src [count] fp32, dst [count] fp32 or bf16 (dtype, rounded to nearest even),
- * both device, not overlapping; arrays with count 0 are skipped. */
+ * both device, not overlapping; arrays with count 0 are skipped. At most 2^24
+ * blocks of 4,096 elements together (RNNT_EUNSUPPORTED beyond). */
 #define RNNT_MAX_SCALED 8
 typedef struct rnnt_scaled {
   const float* src;

@@ -950,10 +950,12 @@ int rnnt_scale_gradients(int32_t n, const rnnt_scaled* arrays, const float* fact
   if (n < 0 || n > RNNT_MAX_SCALED) return fail(RNNT_EINVAL, "n = %d outside [0, %d]", n, RNNT_MAX_SCALED);
   if (n > 0 && (!arrays || !factor)) return fail(RNNT_EINVAL, "arrays and factor are required");
   ScaledArrays a{};
+  long long blocks = 0;
   for (int k = 0; k < n; ++k) {
     const rnnt_scaled& x = arrays[k];
     if (x.count < 0) return fail(RNNT_EINVAL, "array %d: count must be >= 0", k);
     if (x.count > (1ll << 40)) return fail(RNNT_EUNSUPPORTED, "array %d is too large", k);
+    blocks += scale_gradients_blocks((size_t)x.count);
     if (x.dtype != RNNT_F32 && x.dtype != RNNT_BF16) return fail(RNNT_EINVAL, "dtype must be RNNT_F32 or RNNT_BF16");
     if (x.count == 0) continue;
     if (!x.src || !x.dst) return fail(RNNT_EINVAL, "array %d: src and dst are required", k);
@@ -963,6 +965,8 @@ int rnnt_scale_gradients(int32_t n, const rnnt_scaled* arrays, const float* fact
     a.bf16[a.n] = x.dtype == RNNT_BF16;
     ++a.n;
   }
+  // a launch's threads (256 a block) are counted in 32 bits
+  if (blocks > 0xffffffffll / 256) return fail(RNNT_EUNSUPPORTED, "the arrays are too large for one launch");
   return hip_status(launch_scale_gradients(a, factor, divisor, static_cast<hipStream_t>(stream)), "rnnt_scale_gradients");
 }
 

@@ -242,6 +242,7 @@ struct ScaledArrays {
   unsigned char bf16[kMaxScaled], vec[kMaxScaled];
   int n;
 };
+long long scale_gradients_blocks(size_t count);  // blocks of one array
 hipError_t launch_scale_gradients(ScaledArrays a, const float* factor, float divisor, hipStream_t s);
 
 // ---- generic fills -----------------------------------------------------------

@@ -179,12 +179,14 @@ __global__ __launch_bounds__(kValThreads) void scale_gradients_kernel(ScaledArra
 
 }  // namespace
 
+long long scale_gradients_blocks(size_t count) { return (long long)((count + kScalePerBlock - 1) / kScalePerBlock); }
+
 hipError_t launch_scale_gradients(ScaledArrays a, const float* factor, float divisor, hipStream_t s) {
   int blocks = 0;
   for (int k = 0; k < a.n; ++k) {
     a.first[k] = blocks;
     a.vec[k] = ((uintptr_t)a.src[k] & 15) == 0 && ((uintptr_t)a.dst[k] & (a.bf16[k] ? 7 : 15)) == 0;
-    blocks += (int)((a.count[k] + kScalePerBlock - 1) / kScalePerBlock);
+    blocks += (int)scale_gradients_blocks(a.count[k]);  // (their sum is checked by the entry point)
   }
   a.first[a.n] = blocks;
   if (blocks == 0) return hipSuccess;

@@ -86,6 +86,16 @@ def _err(L):
     return L.rnnt_last_error().decode()
 
 
+def test_scaled_gradients_of_more_elements_than_one_launch_takes(L):
+    """Each array within its own limit, their blocks together beyond a launch: refused on the host (the block count
+    used to wrap around to nothing to do)."""
+    from paper_2206_13236_amd import _native as N
+    for n, count in ((8, 1 << 40), (1, 1 << 37), (8, 1 << 34)):
+        arrays = (N.RnntScaled * 8)(*[(0x10000, 0x20000, count, N.RNNT_F32)] * n)
+        assert L.rnnt_scale_gradients(n, arrays, 0x30000, 1.0, None) == N.RNNT_EUNSUPPORTED
+    assert L.rnnt_scale_gradients(0, None, None, 1.0, None) == N.RNNT_OK
+
+
 def test_validation_statuses(L):
     from paper_2206_13236_amd import _native as N
     b = _batch()
