@@ -400,11 +400,11 @@ __global__ __launch_bounds__(kPrepThreads) void joiner_prep_kernel(JoinerArgs a,
       if (SP && a.rsc) a.rsc[(size_t)(off + t) * S + s] = rs;
     }
   }
-  if (pb.hj == 0) return;
   // h of the block's rows, kPrepHGroups groups of 8 columns from its part on
+  const int m0 = off * S + i0, rows = min(min(256, Tn * S - i0), pb.hrows - m0);
+  if (pb.hj == 0 || rows <= 0) return;
   s_info[threadIdx.x] = r;
   __syncthreads();
-  const int m0 = off * S + i0, rows = min(min(256, Tn * S - i0), pb.hrows - m0);
   const int ng = h_groups<SP>(J), g0 = part * kPrepHGroups;
   const EncDec<typename In<SP>::T> ed(a);
   constexpr int NI = kHItems<SP>;
@@ -1726,6 +1726,17 @@ int joiner_bwd_splits(int J, int V, int chunk_rows, int bf16) {
 
 int joiner_db_rows(int chunk_rows) { return (chunk_rows + kTileRows - 1) / kTileRows * (kTileRows / kDbRows); }
 
+// Whether the forward's first h pass runs in the prep kernel's blocks: these
+// cover every padded row, so it does while the first chunk is at least a
+// quarter of them (a launch less: step at N = 32, T = 500 643 -> 633 us, three
+// chunks); beyond, most would have no rows of it, and their number times J / 64
+// would pass what a launch can hold.
+constexpr int kPrepHChunks = 4;
+static bool fwd_h_in_prep(const JoinerArgs& a) {
+  return (long long)a.b.N * a.b.T * a.S <= (long long)kPrepHChunks * a.chunk_rows;
+}
+static hipError_t launch_tail(const JoinerArgs& a, const TailRanges& tr, hipStream_t s, const char* name);
+
 hipError_t launch_joiner_prep(const JoinerArgs& a, hipStream_t s) {
   {
     RNNT_PROF(s, "joiner_prep");
@@ -1737,7 +1748,7 @@ hipError_t launch_joiner_prep(const JoinerArgs& a, hipStream_t s) {
       if (a.wt) pb.wt = (a.V + kWtCols - 1) / kWtCols;
       if (a.wn) pb.wn = a.J;
     }
-    if (a.px) {  // the forward: h of its first chunk
+    if (a.px && fwd_h_in_prep(a)) {
       pb.hj = ((a.bf16 ? h_groups<false>(a.J) : h_groups<true>(a.J)) + kPrepHGroups - 1) / kPrepHGroups;
       pb.hrows = a.chunk_rows;
     }
@@ -1754,8 +1765,8 @@ hipError_t launch_joiner_fwd(const JoinerArgs& a, hipStream_t s) {
   const int nch = (mmax + C - 1) / C;
   auto lo = [&](int k) { return k * C; };
   auto hi = [&](int k) { return (k + 1) * C < mmax ? (k + 1) * C : mmax; };
-  // h of chunk k in slot k % 2; chunk 0's was written by the prep kernel, that
-  // of chunk k + 1 comes from the trailing blocks of chunk k's GEMM launch
+  // h of chunk k in slot k % 2; chunk 0's was written by the prep kernel (or is
+  // by a launch of its own), that of chunk k + 1 comes from the trailing blocks of chunk k's GEMM launch
   // (they write the slot chunk k - 1's launch read)
   auto slot = [&](int k) {
     JoinerArgs c = a;
@@ -1766,6 +1777,12 @@ hipError_t launch_joiner_fwd(const JoinerArgs& a, hipStream_t s) {
   const bool wide = a.V >= kFwdWideV && a.ldh <= (1 << 20);
   const int bm = wide ? CfgWide<false>::BM : kTileRows, bn = wide ? CfgWide<false>::BN : kTileCols;
   const int nt = wide ? CfgWide<false>::NT : kGemmThreads;
+  if (!fwd_h_in_prep(a)) {
+    TailRanges tr{};
+    tr.h0 = h_pass(slot(0), lo(0), hi(0), kTailThreads);
+    const hipError_t e = launch_tail(a, tr, s, "joiner_h");
+    if (e != hipSuccess) return e;
+  }
   for (int k = 0; k < nch; ++k) {
     const int cm0 = lo(k), cm1 = hi(k);
     const JoinerArgs c = slot(k);

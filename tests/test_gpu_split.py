@@ -172,3 +172,25 @@ def test_split_forward_with_an_infinite_weight(J, V):
     on = on & (ranges <= b.u_len[:, None, None])
     nan = np.isnan(host(jo["logits"])[on])
     assert nan[:, v0].all() and nan.sum() == on.sum() and np.isnan(host(pl["loss"])).all()
+
+
+@pytest.mark.parametrize("T,dtype", [(1300, "f32"), (1700, "f32"), (2900, "bf16")], ids=["four_chunks", "five_chunks", "bf16"])
+def test_forward_of_many_row_chunks(T, dtype):
+    """Padded rows of up to four forward chunks, whose first h pass runs in the prep kernel's blocks, and of more, where
+    it is a launch of its own: bitwise the same as each utterance in a batch of its own (one chunk)."""
+    N, U, S, J, V = 6, 9, 8, 16, 19
+    say(f"[split] {N * T * S} rows {dtype}")
+    g = torch.Generator(device="cuda").manual_seed(T)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    enc, dec, W, bias = (torch.randn(s, generator=g, device="cuda").to(dt) for s in ((N, T, J), (N, U + 1, J), (J, V), (V,)))
+    t_len = dev_i32([T, T - 700, T, 5, T - 1, T - 300])
+    u_len, sym = dev_i32([U, 3, U, 4, 0, U]), torch.randint(1, V, (N, U), generator=g, device="cuda", dtype=torch.int32)
+    rg = (torch.arange(T, device="cuda")[None, :, None] * (u_len[:, None, None] - S + 1).clamp(min=0) // T).int()
+    rg = (rg + torch.arange(S, device="cuda", dtype=torch.int32)).contiguous()
+    jo = P.rnnt_pruned_joiner(P.Batch(t_len, u_len, sym, T, U), S, enc, dec, W, bias, rg)
+    for n in range(N):
+        one = P.Batch(t_len[n:n + 1], u_len[n:n + 1], sym[n:n + 1], T, U)
+        ref = P.rnnt_pruned_joiner(one, S, enc[n:n + 1], dec[n:n + 1], W, bias, rg[n:n + 1])
+        torch.cuda.synchronize()
+        for k in ("px", "py", "lse"):
+            assert torch.equal(jo[k][n:n + 1], ref[k]), (k, n)
