@@ -1162,9 +1162,9 @@ __global__ __launch_bounds__(256) void dlm_epi_kernel(SimpleArgs a) {
 // ---------------------------------------------------------------------------
 // d am and d lm in one pass (U + 1 <= 320).
 //
-// One workgroup per (utterance, 64 columns of v, range of frames): groups of
-// eight waves (two groups at U + 1 <= 128, for four waves a SIMD; their
-// registers allow one above) that take the range's steps of 32 frames in turn.
+// One workgroup per (utterance, 64 columns of v, range of frames): one or two
+// groups (sg_groups) of eight waves that take the range's steps of 32 frames in
+// turn.
 // Wave w of a group holds the 16 columns of block w >> 1, and of a step computes
 //   d am [16 x 16] = W [16 x U+1] . e^{lm - m_l} [U+1 x 16], the frames whose
 //     bit 2 is w & 1, finished at once (times e^{am - m_a}, minus the target
@@ -1173,41 +1173,47 @@ __global__ __launch_bounds__(256) void dlm_epi_kernel(SimpleArgs a) {
 //     [32 x 16], kept in registers, added over the groups at the end and
 //     finished (a single range) or stored as the range's partial sums for
 //     dlm_epi_kernel.
-// Both contractions run on three bf16 planes per operand. Only W's planes go
+// Both contractions run on three bf16 planes per operand. W's planes go
 // through LDS: rows for d am, the same rows read transposed
-// (ds_read_b64_tr_b16) for d lm. e^{lm - m_l} is formed once a wave, into
-// the fragments that it keeps, and e^{am - m_a} by the lanes that use it, as
+// (ds_read_b64_tr_b16) for d lm. e^{lm - m_l} is formed once, into LDS at
+// U + 1 <= 128 and above into the fragments that a wave keeps (whose registers
+// then allow two waves a SIMD), and e^{am - m_a} by the lanes that use it, as
 // d lm's fragment (column l16, frames 8 g4 .. + 7), whose frames
 // 8 g4 + 4 (w & 1) .. + 3 are also those of the lane's d am results: d am's
 // tile takes its rows in that order. A step's loads are in flight during the
-// step before; W's planes have two stages a group, one barrier a step.
+// step before; W's planes have two stages a group, one barrier a step, but one
+// stage and two barriers for one group at 64 < U + 1 <= 128, where two
+// workgroups then fit a CU's LDS.
 // (The step is bound by its waves' chains: fragment reads, exponentials and
-// splits, MFMAs. N = 32, T = 500, U = 100, V = 500: 46 us, 63 with fp32 MFMA
-// and both operands in LDS; U = 300, V = 8000, N = 8, T = 1000: 1030 against
-// 1360; V = 4999, U = 77, N = 6, T = 287: 52 against 49, the LDS holding one
-// workgroup a CU. Smoothed, N = 13, T = 333, U = 71, V = 1031: 43 us, the
-// two kernels it replaces 50 and twice the partial sums.)
+// splits, MFMAs. Against fp32 MFMA with both operands in LDS, us with the column
+// sums: N = 32, T = 500, U = 100, V = 500 46 for 66; N = 6, T = 287, U = 77,
+// V = 4999 46 for 51; N = 16, T = 300, U = 80, V = 5000 96 for 120; N = 32,
+// T = 100, U = 30, V = 8000 93 for 101; U = 300, V = 8000, N = 8, T = 1000 1,030
+// for 1,360; but N = 8, T = 500, U = 100, V = 8000 156 for 143. Smoothed, N = 13,
+// T = 333, U = 71, V = 1031: 44 for 180 with the two kernels it replaces and the
+// acoustic statistics that they always formed.)
 // ---------------------------------------------------------------------------
 constexpr int kSgT = 32;        // frames per step
 constexpr int kSgMaxU1 = 320;   // the fused kernel takes U + 1 up to this
 constexpr int kSgV = 64;        // columns per workgroup
 constexpr int kSgThreads = 512; // of a group
 constexpr int kSgList = 24;     // listed targets whose gx one gather round stages (at KP = 128 the LDS is full)
-constexpr int sg_groups(int KP) { return KP <= 128 ? 2 : 1; }
 
-template <int KP>  // u extent staged: U + 1 <= KP (a multiple of 64)
+template <int KP, int GRP_>  // u extent staged: U + 1 <= KP (a multiple of 64); groups of eight waves
 struct alignas(16) SgSmem {
   static constexpr int ROWB = KP * 2;         // bytes per row of a plane
   static constexpr int PLANE = kSgT * ROWB;
-  static constexpr int GRP = sg_groups(KP), WAVES = GRP * kSgThreads / 64;
+  static constexpr int GRP = GRP_, WAVES = GRP * kSgThreads / 64;
   struct Stage {
     unsigned char w[3 * PLANE];     // planes of W(t, u) of the step's frames, [t][u] (zero past ldw)
     float g[kSgList * kSgT];        // gx(t, u_k) of listed targets, [k][t]
     double ry[kSgT];                // row sums of gy
     float ma[kSgT];                 // m_a, +inf past T_n (zero exponentials)
     float br[kSgT], za[kSgT];       // smoothed: weight and lse of the acoustic joiner
-  } st[GRP][2];
-  static constexpr bool EL = GRP == 2;  // e^{lm - m_l} staged here, not in registers
+  };
+  static constexpr int NST = GRP == 1 && KP == 128 ? 1 : 2;  // two workgroups' LDS on a CU
+  Stage st[GRP][NST];
+  static constexpr bool EL = KP <= 128;  // e^{lm - m_l} staged here, not in registers
   static constexpr int EPLANE = kSgV * ROWB;
   unsigned char el[EL ? 3 * EPLANE : 16];
   uint16_t lu[KP];                  // targets in the columns (ascending u)
@@ -1269,8 +1275,9 @@ DEV void sg_load(const SgSrc& c, int t0, const uint16_t* lu, SgPrefetch<KP>& f) 
   }
 }
 
-template <int KP, bool SM>
-DEV void sg_store(const SgSrc& c, typename SgSmem<KP>::Stage& st, const SgPrefetch<KP>& f, int t0) {
+template <int KP, bool SM, int GRP>
+DEV void sg_store(const SgSrc& c, typename SgSmem<KP, GRP>::Stage& st, const SgPrefetch<KP>& f, int t0) {
+  using Smem = SgSmem<KP, GRP>;
   const int tid = threadIdx.x % kSgThreads;
 #pragma unroll
   for (int i = 0; i < SgPrefetch<KP>::NW; ++i) {
@@ -1280,10 +1287,10 @@ DEV void sg_store(const SgSrc& c, typename SgSmem<KP>::Stage& st, const SgPrefet
     uint4 p0, p1, p2;
     split3(x, p0, p1, p2);
     if (r < kSgT) {
-      unsigned char* d = st.w + SgSmem<KP>::pos(r, q % (KP / 8));
+      unsigned char* d = st.w + Smem::pos(r, q % (KP / 8));
       *reinterpret_cast<uint4*>(d) = p0;
-      *reinterpret_cast<uint4*>(d + SgSmem<KP>::PLANE) = p1;
-      *reinterpret_cast<uint4*>(d + 2 * SgSmem<KP>::PLANE) = p2;
+      *reinterpret_cast<uint4*>(d + Smem::PLANE) = p1;
+      *reinterpret_cast<uint4*>(d + 2 * Smem::PLANE) = p2;
     }
   }
 #pragma unroll
@@ -1313,10 +1320,10 @@ DEV void sg_planes(const float (&x)[8], bf16x8 (&f)[3]) {
   f[2] = __builtin_bit_cast(bf16x8, p2);
 }
 
-template <int KP, bool SM>  // SM: smoothed
-__global__ __launch_bounds__(kSgThreads * sg_groups(KP)) void simple_grad_kernel(SimpleArgs a, int splits, int items) {
-  using Smem = SgSmem<KP>;
-  constexpr int NS = KP / 32, NUB = KP / 32, GRP = Smem::GRP, NT = GRP * kSgThreads;
+template <int KP, bool SM, int GRP>  // SM: smoothed
+__global__ __launch_bounds__(kSgThreads * GRP, KP <= 128 ? 4 : 1) void simple_grad_kernel(SimpleArgs a, int splits, int items) {
+  using Smem = SgSmem<KP, GRP>;
+  constexpr int NS = KP / 32, NUB = KP / 32, NT = GRP * kSgThreads;
   __shared__ Smem sm;
   const int T = a.b.T, U1 = a.b.U + 1, V = a.V, blank = a.b.blank;
   // an eighth of the items, in order, to each XCD: the column tiles of a frame
@@ -1351,8 +1358,8 @@ __global__ __launch_bounds__(kSgThreads * sg_groups(KP)) void simple_grad_kernel
   const int vb = (wave >> 1) & 3;
   const int erow = (l16 & 3) | ((l16 >> 2) << 3) | ((vb & 1) << 2) | ((vb >> 1) << 5);
   if constexpr (Smem::EL) {
-    const int b = wave & 3, c = (wave >> 2) * 4 + g4;
-    if (c < KP / 8) {
+#pragma unroll
+    for (int b = wave & 3, c = (wave >> 2) * 4 + g4; c < KP / 8; c += NT / 64) {
       float e[8];
       sg_load8(lmn, V, 8 * c, v0 + 16 * b + l16, e);
 #pragma unroll
@@ -1431,7 +1438,7 @@ __global__ __launch_bounds__(kSgThreads * sg_groups(KP)) void simple_grad_kernel
     const int t0 = (s0 + grp) * kSgT;
     sg_load8(src.am, V, t0 + 8 * g4, vw, x);
     sg_load<KP, SM>(src, t0, sm.lu, f);
-    sg_store<KP, SM>(src, sm.st[grp][0], f, t0);
+    sg_store<KP, SM, GRP>(src, sm.st[grp][0], f, t0);
     // (x is waited for here: otherwise the loop's first use of it also waits, each
     // step, for the stores of the step before)
 #pragma unroll
@@ -1444,8 +1451,8 @@ __global__ __launch_bounds__(kSgThreads * sg_groups(KP)) void simple_grad_kernel
   int pt = Smem::pos(8 * g4 + (l16 >> 2), 2 * h + ((l16 & 3) >> 1)) + (l16 & 1) * 8;
   for (int st = s0; st < s1; st += GRP) {
     const int t0 = (st + grp) * kSgT, tn = t0 + GRP * kSgT;
-    typename Smem::Stage& cur = sm.st[grp][((st - s0) / GRP) & 1];
-    typename Smem::Stage& nxt = sm.st[grp][(((st - s0) / GRP) & 1) ^ 1];
+    typename Smem::Stage& cur = sm.st[grp][((st - s0) / GRP) & (Smem::NST - 1)];
+    typename Smem::Stage& nxt = sm.st[grp][((st - s0) / GRP + 1) & (Smem::NST - 1)];
     sg_barrier();  // the step's stage is written, the other one's reads are done
     floatx4 accd = floatx4{0.f, 0.f, 0.f, 0.f};
     float ed[4], xd[4];  // e^{am - m_a} and am of the lane's d am results
@@ -1525,7 +1532,8 @@ __global__ __launch_bounds__(kSgThreads * sg_groups(KP)) void simple_grad_kernel
     for (int r = 0; r < 4; ++r)
       __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sc * res[r]), gout,
                                             (int)(t0 + tl + r < Te ? (uint32_t)((t0 + tl + r) * V) * 4u + ov : kOob), 0, 0);
-    sg_store<KP, SM>(src, nxt, f, tn);
+    if constexpr (Smem::NST == 1) sg_barrier();  // every read of the stage is done
+    sg_store<KP, SM, GRP>(src, nxt, f, tn);
   }
   // the groups' d lm sums: group g finishes the blocks i of parity g (all of
   // them where there is one group), the other's come through LDS
@@ -1640,12 +1648,32 @@ int dlm_splits(int N, int T, int U, int V) {
 // U = 60, V = 500: the step 314 -> 306 us; smoothed, N = 13, T = 333, U = 71,
 // V = 1031: 521 -> 511 us).
 constexpr int kSgBlocks = 256;
+
+// Groups of a workgroup for U + 1 <= 128. Two share e^{lm - m_l} and halve an
+// item's steps, but fill a CU; of one, two workgroups share a CU, so that one
+// works while the other starts or ends. Where one group a workgroup would leave
+// half of the chip's waves empty (up to 256 items), two win: N = 32, T = 500,
+// U = 100, V = 500 46 us with the column sums against 60, N = 2, T = 300, U = 80,
+// V = 5000 30 against 38. Beyond, one wins at U + 1 <= 64 (N = 8, T = 300,
+// U = 50, V = 5000, 632 items: 56 against 64; N = 32, T = 100, U = 30, V = 8000,
+// 4,000 items: 93 against 157). At 64 < U + 1 <= 128, with one stage of W, an
+// item of two takes about 0.6 of the time of one, and the chip takes 256 or 512
+// items at a time: one wins unless it leaves its last round half empty (N = 6,
+// T = 287, U = 77, V = 4999, 474 items: 46 against 53; N = 16, T = 300, U = 80,
+// V = 5000, 1,264 items: 97 against 112; but N = 24, T = 400, U = 90, V = 2000,
+// 768 items: 89 against 85).
+static int sg_groups(int N, int U, int V) {
+  if (U + 1 > 128) return 1;
+  const long long items = (long long)N * ((V + kSgV - 1) / kSgV);
+  if (U + 1 <= 64) return items > 256 ? 1 : 2;
+  return 5 * ((items + 511) / 512) <= 3 * ((items + 255) / 256) ? 1 : 2;
+}
 int simple_grad_splits(int N, int T, int U, int V) {
   // one utterance's am and lm must stay below 2^31 bytes, the rows that a tile reaches past them included (32-bit offsets)
   if (U + 1 > kSgMaxU1 || (long long)(T + kSgMaxU1) * V * 4 >= (1ll << 31)) return 0;
   const long long base = (long long)N * ((V + kSgV - 1) / kSgV);
   const int steps = (T + kSgT - 1) / kSgT;
-  const int want = kSgBlocks / sg_groups(U + 1 <= 128 ? 128 : kSgMaxU1);
+  const int want = kSgBlocks / sg_groups(N, U, V);
   long long s = (want + base - 1) / base;
   if (s > steps) s = steps;
   return s < 1 ? 1 : (int)s;
@@ -1716,13 +1744,13 @@ hipError_t launch_smoothing_stats(const SimpleArgs& a, hipStream_t s) {
 }
 
 // u extent KP: the smallest of 64, 128, 192, 320 that holds U + 1 (LDS and
-// the d lm accumulators scale with it)
-template <int KP>
+// the d lm accumulators scale with it); GRP: sg_groups
+template <int KP, int GRP>
 static void launch_simple_grad(const SimpleArgs& a, int gs, hipStream_t s) {
   const int items = a.b.N * gs * ((a.V + kSgV - 1) / kSgV);
-  const dim3 grid((items + 7) / 8 * 8), block(kSgThreads * sg_groups(KP));
-  if (a.lm_only != 0.f || a.am_only != 0.f) hipLaunchKernelGGL((simple_grad_kernel<KP, true>), grid, block, 0, s, a, gs, items);
-  else hipLaunchKernelGGL((simple_grad_kernel<KP, false>), grid, block, 0, s, a, gs, items);
+  const dim3 grid((items + 7) / 8 * 8), block(kSgThreads * GRP);
+  if (a.lm_only != 0.f || a.am_only != 0.f) hipLaunchKernelGGL((simple_grad_kernel<KP, true, GRP>), grid, block, 0, s, a, gs, items);
+  else hipLaunchKernelGGL((simple_grad_kernel<KP, false, GRP>), grid, block, 0, s, a, gs, items);
 }
 
 hipError_t launch_simple_grads(const SimpleArgs& a, hipStream_t s) {
@@ -1742,10 +1770,11 @@ hipError_t launch_simple_grads(const SimpleArgs& a, hipStream_t s) {
   if (gs > 0 && a.am_grad && a.lm_grad) {
     {
       RNNT_PROF(s, "simple_grad");
-      if (U1 <= 64) launch_simple_grad<64>(a, gs, s);
-      else if (U1 <= 128) launch_simple_grad<128>(a, gs, s);
-      else if (U1 <= 192) launch_simple_grad<192>(a, gs, s);
-      else launch_simple_grad<kSgMaxU1>(a, gs, s);
+      const bool two = sg_groups(a.b.N, a.b.U, V) == 2;
+      if (U1 <= 64) two ? launch_simple_grad<64, 2>(a, gs, s) : launch_simple_grad<64, 1>(a, gs, s);
+      else if (U1 <= 128) two ? launch_simple_grad<128, 2>(a, gs, s) : launch_simple_grad<128, 1>(a, gs, s);
+      else if (U1 <= 192) launch_simple_grad<192, 1>(a, gs, s);
+      else launch_simple_grad<kSgMaxU1, 1>(a, gs, s);
     }
     if (gs > 1 || smooth) {
       SimpleArgs e = a;

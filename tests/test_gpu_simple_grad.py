@@ -34,7 +34,9 @@ def _case(N, T, U, V, spread=1.0):
 @pytest.mark.parametrize("N,T,U,V,spread", [
     (2, 31, 63, 70, 1.0), (2, 33, 64, 65, 1.0), (2, 65, 127, 16, 1.0), (2, 40, 128, 131, 1.0), (2, 64, 191, 64, 1.0),
     (2, 34, 192, 100, 1.0), (2, 5, 319, 130, 1.0), (2, 70, 319, 33, 1.0), (2, 34, 320, 70, 1.0), (2, 400, 20, 66, 1.0),
-    (2, 97, 90, 9000, 1.0), (2, 1, 1, 3, 1.0), (2, 100, 40, 129, 10.0), (2, 90, 150, 67, 10.0), (300, 40, 5, 20, 1.0)])
+    (2, 97, 90, 9000, 1.0), (2, 1, 1, 3, 1.0), (2, 100, 40, 129, 10.0), (2, 90, 150, 67, 10.0), (300, 40, 5, 20, 1.0),
+    # more than 256 items: one group a workgroup, more targets than one gather round lists
+    (300, 70, 60, 20, 1.0), (300, 66, 63, 3, 10.0), (300, 65, 100, 30, 1.0), (300, 34, 127, 60, 10.0)])
 def test_simple_gradients_over_own_occupations(N, T, U, V, spread):
     say(f"[simple_grad] N={N} T={T} U={U} V={V} spread={spread}")
     b = _case(N, T, U, V, spread)
@@ -65,7 +67,8 @@ def test_simple_gradients_over_own_occupations(N, T, U, V, spread):
 
 
 @pytest.mark.parametrize("w", [(0.25, 0.1), (0.4, 0.0), (0.0, 0.3)], ids=["both", "lm", "am"])
-@pytest.mark.parametrize("N,T,U,V", [(2, 33, 63, 37), (2, 40, 64, 130), (2, 34, 128, 66), (2, 33, 200, 65)])
+@pytest.mark.parametrize("N,T,U,V", [(2, 33, 63, 37), (2, 40, 64, 130), (2, 34, 128, 66), (2, 33, 200, 65),
+                                     (2, 34, 63, 8300), (2, 33, 100, 8300)])  # more than 256 items
 def test_smoothed_gradients(N, T, U, V, w):
     say(f"[simple_grad] smoothed {w} N={N} T={T} U={U} V={V}")
     b = _case(N, T, U, V)
