@@ -412,6 +412,12 @@ typedef struct rnnt_step {
 } rnnt_step;
 int rnnt_train_step(const rnnt_batch* batch, const rnnt_step* step, void* stream);
 
+/* rnnt_train_step from the pruned loss and the simple loss's gradients on: the
+ * caller has enqueued rnnt_simple_loss (without gradients), rnnt_prune_ranges
+ * and rnnt_pruned_joiner_ex with the step's arguments on `stream`, for instance
+ * before allocating what only the later stages need. */
+int rnnt_train_step_rest(const rnnt_batch* batch, const rnnt_step* step, void* stream);
+
 /* dst = src * (factor[0] * (1 / divisor)) for up to RNNT_MAX_SCALED arrays in one
  * launch: stored gradients times an incoming one. factor [1] fp32 device;
  * src [count] fp32, dst [count] fp32 or bf16 (dtype, rounded to nearest even),

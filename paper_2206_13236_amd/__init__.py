@@ -500,19 +500,17 @@ class PrunedRnntLoss:
             self._side[key] = (stream, events)
         return self._side[key]
 
-    def _sizes(self, N, T, U, V, S, J, dt):
-        """Workspace bytes, the backward's chunk request and the head's rows: functions of these sizes and of the
-        module's options only."""
-        key = (N, T, U, V, S, J, dt, self.keep_logits, self.keep_head, self.bwd_chunk_rows)
+    def _sizes(self, key):
+        """Workspace bytes, the backward's chunk request and the head's rows: functions of the key's sizes and options."""
         got = self._size_cache.get(key)
         if got is None:
-            chunk = self.bwd_chunk_rows
-            if self.keep_logits and chunk == 0:
+            N, T, U, V, S, J, dt, keep_logits, keep_head, chunk = key
+            if keep_logits and chunk == 0:
                 # the caller keeps all the logits anyway: one chunk of every row
                 # (fewer, fuller launches) unless that breaks the 32-bit limit
                 whole = (N * T * S + 127) // 128 * 128
                 chunk = whole if backward_chunk_rows(N, T, S, J, V, dt, whole) else 0
-            head = not self.keep_logits and self.keep_head
+            head = not keep_logits and keep_head
             got = (simple_loss_workspace_size(N, T, U, V),
                    max(pruned_joiner_workspace_size(N, T, S, J, V, dt), pruned_loss_workspace_size(N, T, U, S),
                        pruned_joiner_backward_workspace_size(N, T, U, S, J, V, dt, chunk)),
@@ -542,28 +540,64 @@ class PrunedRnntLoss:
 
         _need(am, "am", f32, (N, T, V))
         _need(lm, "lm", f32, (N, U + 1, V))
-        n_simple, n_pruned, chunk, head_rows = self._sizes(N, T, U, V, S, J, dt)
+        lat, band = (N, T, U + 1), (N, T, S)
+        if self.pruned_scale != 0.0:
+            _need(enc, "enc", W.dtype, (N, T, J))
+            _need(dec, "dec", W.dtype, (N, U + 1, J))
+            _need(W, "W", W.dtype, (J, V))
+            if bias is not None:
+                _need(bias, "bias", W.dtype, (V,))
+            # arrays that a later stage reads back have their shape, the others room for what is written
+            back = {"simple_loss": (N,), "pruned_loss": (N,), "simple_px_occ": lat, "simple_py_occ": lat, "ranges": band,
+                    "px": band, "py": band, "lse": band, "pruned_px_occ": band, "pruned_py_occ": band}
+            if self.keep_logits:
+                back["logits"] = (N, T, S, V)
+            written = {"am_grad": (N, T, V), "lm_grad": (N, U + 1, V), "enc_grad": (N, T, J), "dec_grad": (N, U + 1, J),
+                       "W_grad": (J, V), "bias_grad": (V,), "loss": (N,), "total": ()}
+            for name, t in out.items():
+                if name in written:
+                    _array(t, name, f32, *written[name])
+                elif name in back and t is not None:
+                    _need(t, name, torch.int32 if name == "ranges" else f32, back[name])
+        key = (N, T, U, V, S, J, dt, self.keep_logits, self.keep_head, self.bwd_chunk_rows)
+        sizes, kept = self._size_cache.get(key), self._cache.get("ws_pruned")
+        # a module's first step, or its first of these sizes: the stages up to the joiner are enqueued one by one, so
+        # that what the later ones need is allocated, and the second stream set up, beside them and not before them
+        # (N = 32, T = 500, U = 100, V = 500, nothing allocated yet: 957 us with all of it before them, 763 so)
+        fresh = sizes is None or kept is None or kept.numel() != sizes[1] or kept.device != dev
+        n_simple = simple_loss_workspace_size(N, T, U, V) if fresh else sizes[0]
         ws_s = self._buf("ws_simple", (n_simple,), torch.uint8, dev)
-        ws_p = self._buf("ws_pruned", (n_pruned,), torch.uint8, dev)
         ssc = self._buf("ssc", (N,), f32, dev)
         psc = self._buf("psc", (N,), f32, dev)
-        if self._cache.get("scales") != (N, self.simple_scale, self.pruned_scale):
+        if self._cache.get("scales") != (N, dev, self.simple_scale, self.pruned_scale):
             with torch.cuda.stream(main):
                 ssc.fill_(self.simple_scale)
                 psc.fill_(self.pruned_scale)
-            self._cache["scales"] = (N, self.simple_scale, self.pruned_scale)
-        lat, band = (N, T, U + 1), (N, T, S)
+            self._cache["scales"] = (N, dev, self.simple_scale, self.pruned_scale)
         res = {"simple_loss": o("simple_loss", (N,)), "simple_px_occ": o("simple_px_occ", lat),
-               "simple_py_occ": o("simple_py_occ", lat), "am_grad": o("am_grad", (N, T, V)),
-               "lm_grad": o("lm_grad", (N, U + 1, V)), "enc_grad": o("enc_grad", (N, T, J)),
-               "dec_grad": o("dec_grad", (N, U + 1, J)), "W_grad": o("W_grad", (J, V)), "bias_grad": o("bias_grad", (V,))}
-
-        if self.pruned_scale == 0.0:
-            # warm-up: the pruned part carries no weight and is not evaluated
+               "simple_py_occ": o("simple_py_occ", lat)}
+        if fresh or self.pruned_scale == 0.0:
             rnnt_simple_loss(
                 batch, V, am, lm, ssc, loss=res["simple_loss"], px_occ=res["simple_px_occ"],
                 py_occ=res["simple_py_occ"], workspace=ws_s, stream=main, lm_only_scale=self.lm_only_scale,
                 am_only_scale=self.am_only_scale)
+        if self.pruned_scale != 0.0:
+            _, n_pruned, chunk, head_rows = self._sizes(key)
+            res["ranges"] = o("ranges", band, torch.int32)
+            if fresh:
+                rnnt_prune_ranges(batch, S, res["simple_px_occ"], res["simple_py_occ"], res["ranges"], stream=main)
+            ws_p = self._buf("ws_pruned", (n_pruned,), torch.uint8, dev)
+            res.update(px=o("px", band), py=o("py", band), lse=o("lse", band))
+            logits = o("logits", (N, T, S, V)) if self.keep_logits else None
+            head = self._buf("head", (head_rows, (V + 7) // 8 * 8), f32, dev) if head_rows else None
+            if fresh:
+                rnnt_pruned_joiner(batch, S, enc, dec, W, bias, res["ranges"], px=res["px"], py=res["py"], lse=res["lse"],
+                                   logits=logits, workspace=ws_p, stream=main, head=head, head_rows=head_rows)
+        res.update(am_grad=o("am_grad", (N, T, V)), lm_grad=o("lm_grad", (N, U + 1, V)), enc_grad=o("enc_grad", (N, T, J)),
+                   dec_grad=o("dec_grad", (N, U + 1, J)), W_grad=o("W_grad", (J, V)), bias_grad=o("bias_grad", (V,)))
+
+        if self.pruned_scale == 0.0:
+            # warm-up: the pruned part carries no weight and is not evaluated
             rnnt_simple_loss_backward(
                 batch, V, am, lm, res["simple_px_occ"], ws_s, scale=ssc, am_grad=res["am_grad"],
                 lm_grad=res["lm_grad"], stream=main, lm_only_scale=self.lm_only_scale,
@@ -577,26 +611,8 @@ class PrunedRnntLoss:
                                            loss=o("loss", (N,)), total=o("total", ()), stream=main))
             return res
 
-        _need(enc, "enc", W.dtype, (N, T, J))
-        _need(dec, "dec", W.dtype, (N, U + 1, J))
-        _need(W, "W", W.dtype, (J, V))
-        if bias is not None:
-            _need(bias, "bias", W.dtype, (V,))
-        res.update(pruned_loss=o("pruned_loss", (N,)), ranges=o("ranges", band, torch.int32), px=o("px", band),
-                   py=o("py", band), lse=o("lse", band), pruned_px_occ=o("pruned_px_occ", band),
+        res.update(pruned_loss=o("pruned_loss", (N,)), pruned_px_occ=o("pruned_px_occ", band),
                    pruned_py_occ=o("pruned_py_occ", band), loss=o("loss", (N,)), total=o("total", ()))
-        logits = o("logits", (N, T, S, V)) if self.keep_logits else None
-        # arrays that a later stage reads back have their shape, the others room for what is written
-        back = {"simple_loss": (N,), "pruned_loss": (N,), "simple_px_occ": lat, "simple_py_occ": lat, "ranges": band,
-                "px": band, "py": band, "lse": band, "pruned_px_occ": band, "pruned_py_occ": band, "logits": (N, T, S, V)}
-        written = {"am_grad": (N, T, V), "lm_grad": (N, U + 1, V), "enc_grad": (N, T, J), "dec_grad": (N, U + 1, J),
-                   "W_grad": (J, V), "bias_grad": (V,), "loss": (N,), "total": ()}
-        for key, t in out.items():
-            if key in written:
-                _array(t, key, f32, *written[key])
-            elif key in back and t is not None and (key != "logits" or logits is not None):
-                _need(t, key, torch.int32 if key == "ranges" else f32, back[key])
-        head = self._buf("head", (head_rows, (V + 7) // 8 * 8), f32, dev) if head_rows else None
         # the second stream's events cost more than what it would overlap on small batches
         overlap = self.overlap and N * T * (U + 1) * V >= _OVERLAP_WORK
         side, (fork, lossev, join) = self._side_stream(dev) if overlap else (None, (None,) * 3)
@@ -613,7 +629,8 @@ class PrunedRnntLoss:
             ptr(ws_s), n_simple, ptr(ws_p), n_pruned,
             side.cuda_stream if overlap else None, fork.cuda_event if overlap else None,
             lossev.cuda_event if overlap else None, join.cuda_event if overlap else None)
-        check(lib().rnnt_train_step(batch.c, ctypes.byref(p), _stream(main)))
+        run = lib().rnnt_train_step_rest if fresh else lib().rnnt_train_step
+        check(run(batch.c, ctypes.byref(p), _stream(main)))
         return res
 
 

@@ -114,6 +114,7 @@ SIGNATURES = {
     "rnnt_combine_losses": (c_int32, [c_int32, c_void_p, c_void_p, c_float, c_float, c_int32, c_void_p, c_void_p,
                                       c_void_p]),
     "rnnt_train_step": (c_int32, [POINTER(RnntBatch), POINTER(RnntStep), c_void_p]),
+    "rnnt_train_step_rest": (c_int32, [POINTER(RnntBatch), POINTER(RnntStep), c_void_p]),
     "rnnt_scale_gradients": (c_int32, [c_int32, POINTER(RnntScaled), c_void_p, c_float, c_void_p]),
     "rnnt_validate_inputs": (c_int32, [POINTER(RnntBatch), c_int32, c_int32, c_int32, c_int32, c_void_p, c_void_p,
                                        c_void_p, c_void_p, c_void_p, POINTER(c_int32), c_void_p]),

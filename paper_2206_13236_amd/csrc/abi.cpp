@@ -895,7 +895,7 @@ int rnnt_combine_losses(int32_t N, const float* simple_loss, const float* pruned
   return hip_status(e, "rnnt_combine_losses");
 }
 
-int rnnt_train_step(const rnnt_batch* batch, const rnnt_step* p, void* stream) {
+static int train_step(const rnnt_batch* batch, const rnnt_step* p, void* stream, bool rest) {
   if (!batch || !p) return fail(RNNT_EINVAL, "batch and step are required");
   if (p->side_stream && (!p->fork_event || !p->loss_event || !p->join_event))
     return fail(RNNT_EINVAL, "side_stream needs fork_event, loss_event and join_event");
@@ -907,14 +907,17 @@ int rnnt_train_step(const rnnt_batch* batch, const rnnt_step* p, void* stream) {
     if (e == hipSuccess) e = hipStreamWaitEvent(to, ev, 0);
     return hip_status(e, "rnnt_train_step");
   };
-  int rc = rnnt_simple_loss(batch, p->V, p->am, p->lm, p->simple_scales, p->lm_only_scale, p->am_only_scale,
-                            p->simple_loss, p->simple_px_occ, p->simple_py_occ, nullptr, nullptr, nullptr, nullptr,
-                            p->simple_workspace, p->simple_workspace_bytes, stream);
-  if (!rc) rc = rnnt_prune_ranges(batch, p->S, p->simple_px_occ, p->simple_py_occ, p->ranges, stream);
-  if (!rc)
-    rc = rnnt_pruned_joiner_ex(batch, p->S, p->J, p->V, p->dtype, p->enc, p->dec, p->W, p->bias, p->ranges, p->px, p->py,
-                               p->lse, p->logits, p->head, p->head_rows, p->pruned_workspace, p->pruned_workspace_bytes,
-                               stream);
+  int rc = RNNT_OK;
+  if (!rest) {
+    rc = rnnt_simple_loss(batch, p->V, p->am, p->lm, p->simple_scales, p->lm_only_scale, p->am_only_scale,
+                          p->simple_loss, p->simple_px_occ, p->simple_py_occ, nullptr, nullptr, nullptr, nullptr,
+                          p->simple_workspace, p->simple_workspace_bytes, stream);
+    if (!rc) rc = rnnt_prune_ranges(batch, p->S, p->simple_px_occ, p->simple_py_occ, p->ranges, stream);
+    if (!rc)
+      rc = rnnt_pruned_joiner_ex(batch, p->S, p->J, p->V, p->dtype, p->enc, p->dec, p->W, p->bias, p->ranges, p->px,
+                                 p->py, p->lse, p->logits, p->head, p->head_rows, p->pruned_workspace,
+                                 p->pruned_workspace_bytes, stream);
+  }
   if (!rc && side) rc = order(main, side, p->fork_event);
   if (!rc)
     rc = rnnt_simple_loss_backward(batch, p->V, p->am, p->lm, p->simple_scales, p->lm_only_scale, p->am_only_scale,
@@ -943,6 +946,14 @@ int rnnt_train_step(const rnnt_batch* batch, const rnnt_step* p, void* stream) {
     else rc = jrc;
   }
   return rc;
+}
+
+int rnnt_train_step(const rnnt_batch* batch, const rnnt_step* step, void* stream) {
+  return train_step(batch, step, stream, false);
+}
+
+int rnnt_train_step_rest(const rnnt_batch* batch, const rnnt_step* step, void* stream) {
+  return train_step(batch, step, stream, true);
 }
 
 int rnnt_scale_gradients(int32_t n, const rnnt_scaled* arrays, const float* factor, float divisor, void* stream) {

@@ -49,6 +49,29 @@ def test_step_equals_its_stages(wl, work, monkeypatch):
         assert torch.equal(out[k], r), k
 
 
+@pytest.mark.parametrize("pruned_scale", [1.0, 0.0])
+def test_first_step_of_each_size_equals_the_kept_one(pruned_scale, monkeypatch):
+    """A module's first step, and its first of other sizes, runs its stages up to the joiner by their own calls: every
+    output bitwise that of a module that has its buffers; sizes that come back too."""
+    monkeypatch.setattr(P, "_OVERLAP_WORK", 0)
+    cases = [("bpe", dict(seed=3, N=3, T_range=(30, 61), U_range=(5, 17), V=133, J=72)),
+             ("long", dict(seed=4, N=2, T_range=(20, 41), U_range=(5, 9), V=70, J=40))]
+    step = P.PrunedRnntLoss(5, pruned_scale=pruned_scale)
+    for wl, kw in (cases + cases)[:3]:
+        say(f"[step] first of {wl} {kw} pruned scale {pruned_scale}")
+        b = make_batch(wl, **kw)
+        bf = b.wl.joiner_dtype == "bf16"
+        args = (dev_f32(b.am), dev_f32(b.lm), *(dev_joiner(x, bf) for x in (b.enc, b.dec, b.W, b.bias)))
+        batch, kept = make_dev_batch(b), P.PrunedRnntLoss(5, pruned_scale=pruned_scale)
+        for _ in range(2):
+            ref = kept.step(batch, *args)
+        got = step.step(batch, *args)
+        torch.cuda.synchronize()
+        assert got.keys() == ref.keys()
+        for k, r in ref.items():
+            assert torch.equal(got[k], r), k
+
+
 def test_step_refuses_mismatched_arguments():
     b = make_batch("tiny")
     args = [dev_f32(b.am), dev_f32(b.lm), *(dev_joiner(x, False) for x in (b.enc, b.dec, b.W, b.bias))]
