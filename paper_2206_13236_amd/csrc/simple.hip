@@ -1610,11 +1610,18 @@ static int split_count(long long tiles, int K, int bk) {
   return sk < 1 ? 1 : (int)sk;
 }
 
-// K ranges of the split normaliser: those of the least estimated time. The
+// Whether the fused normaliser takes the call (see launch_normalizer; its
+// offsets within an utterance's am and lm are 32-bit).
+static bool normalizer_fused(int T, int U, int V) {
+  return U + 1 <= kNfMaxU1 && V <= kNfMaxV && (long long)T * V * 4 < (1ll << 31) && (long long)(U + 1) * V * 4 < (1ll << 31);
+}
+
+// K ranges of the split normaliser (0 where the fused one runs, without partial sums): those of the least estimated time. The
 // chip holds 512 workgroups at a time, two on a CU, whose steps then take
 // about 1.75 us each (1.25 us alone on a CU), and every range's partial sums
 // are written and read once (about 5 TB/s); a range is at least four steps.
 int normalizer_splits(int N, int T, int U, int V) {
+  if (normalizer_fused(T, U, V)) return 0;
   const int bn = ns_cols(U + 1);
   const double tiles = (double)N * ((T + kNsT - 1) / kNsT) * ((U + 1 + bn - 1) / bn);
   const int steps = (V + kNsV - 1) / kNsV;
@@ -1687,10 +1694,7 @@ static void launch_normalizer_fused(const SimpleArgs& a, bool v4, unsigned block
 
 hipError_t launch_normalizer(const SimpleArgs& a, hipStream_t s) {
   const int T = a.b.T, U1 = a.b.U + 1;
-  const long long tiles = (long long)a.b.N * ((T + kNfT - 1) / kNfT);
-  const int chunks = (a.V + kNfV - 1) / kNfV;
-  if (U1 <= kNfMaxU1 && a.V <= kNfMaxV && (long long)T * a.V * 4 < (1ll << 31) &&
-      (long long)U1 * a.V * 4 < (1ll << 31) && (tiles >= 192 || chunks <= 16)) {
+  if (normalizer_fused(T, a.b.U, a.V)) {
     // every u of 32 frames per workgroup, the epilogue in the same kernel: the
     // faster one where V is short, so that the epilogue's gathers weigh as much
     // as the contraction (N = 32, T = 500, U = 100, V = 500: 36 us against 22 +

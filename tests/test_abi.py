@@ -76,6 +76,16 @@ def test_workspace_queries(L):
     assert L.rnnt_full_loss_workspace_size(2, 20, 5, 32, 16, N.RNNT_F32) > 0
 
 
+def test_simple_loss_workspace_holds_partial_sums_only_where_they_are_written(L):
+    """The normaliser that forms Z in one kernel (U + 1 <= 128, V <= 1024) leaves no partial sums of [N, T, U + 1]."""
+    N, T, U = 4, 900, 100
+    cells = 4 * N * T * (U + 1)
+    fused, split = (L.rnnt_simple_loss_workspace_size(N, T, U, V) for V in (1024, 1025))
+    other = 4 * (N * (U + 1) * 33 + 2 * N)  # the d lm partials of at most 32 frame ranges and two rows of [N, V]
+    assert split - fused >= cells - other
+    assert L.rnnt_simple_loss_workspace_size(N, T, 128, 1024) > fused + cells  # U + 1 = 129: the split normaliser
+
+
 def _batch(N=2, T=10, U=3):
     from paper_2206_13236_amd._native import RnntBatch
     # fake device addresses: validation never dereferences them
