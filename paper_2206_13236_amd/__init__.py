@@ -444,7 +444,7 @@ class PrunedRnntLoss:
     the pruned recursion, which occupies a few workgroups per utterance; the
     combined loss follows them there once the pruned loss is final (beside
     the joiner backward), and the stream is joined back before ``step``
-    returns (in stream order).
+    returns (in stream order). Small batches stay on the caller's stream.
 
     With ``pruned_scale == 0`` (the warm-up of Sec. 4: the pruned part is
     disabled until the simple loss gives useful bounds) the pruned stages are

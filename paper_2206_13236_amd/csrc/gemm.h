@@ -245,10 +245,12 @@ DEV int tile_col(int j) {
 // ---------------------------------------------------------------------------
 // Main loops with both operands loaded straight from global memory into LDS
 // (buffer_load_dwordx4 ... lds: the 16 bytes of lane i land at the
-// instruction's LDS base + 16 i). Nothing is staged through registers, so a
-// K-step's loads stay in flight at no register cost while the previous
-// K-step computes, and two workgroups share a CU (64 KiB of LDS each at
-// 128 x 128, two stages).
+// instruction's LDS base + 16 i). Nothing is staged through registers, and two
+// workgroups share a CU (64 KiB of LDS each at 128 x 128, two stages). A
+// K-step's loads are issued before the previous K-step's fragments are read,
+// but the compiler takes any LDS read for one of the bytes in flight and waits
+// for them (s_waitcnt vmcnt(0)) before the first of those reads: they overlap
+// the other workgroup's work, not their own workgroup's MFMAs.
 //
 // Two 16-bit operand formats:
 //   bf16   one 16-bit word per element;
@@ -433,9 +435,7 @@ DEV void lds_compute_stage(const unsigned char* As, const unsigned char* Bs, flo
   }
 }
 
-// Waits for this wave's outstanding loads, then meets the other waves. An
-// explicit s_waitcnt + s_barrier rather than __syncthreads(), whose release
-// fence the compiler would also place after the next stage's loads.
+// Waits for this wave's outstanding loads, then meets the other waves.
 DEV void lds_stage_barrier() { asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <class Cfg>
@@ -447,7 +447,7 @@ DEV void zero_acc(floatx4 (&acc)[Cfg::FM][Cfg::FN]) {
 }
 
 // K loop over all words of the rows with two LDS stages: at step kt the loads
-// of step kt+1 run while step kt computes; one barrier per step. Leaves the
+// of step kt+1 go to the other stage; one barrier per step. Leaves the
 // tile in `acc` and LDS free for the caller (it ends with a barrier). Must be
 // called by all NT threads of the workgroup.
 template <class Cfg>
