@@ -243,13 +243,15 @@ struct JoinerBwdWs {
 };
 
 // one_slot: the unpruned loss, whose chunks run one by one through slot 0, so
-// that the rings of the pruned path's pipeline shrink to that one slot.
+// that the rings of the pruned path's pipeline shrink to that one slot; as they
+// do where all rows are one chunk.
 JoinerBwdWs joiner_bwd_layout(void* base, int N, int T, int S, int J, int V, int bf16, int chunk_request = 0,
                               bool one_slot = false) {
   Carve c(base);
   JoinerBwdWs w;
   const size_t M = (size_t)N * T * S;
   w.chunk_rows = joiner_bwd_chunk_rows(N, T, S, J, V, bf16, chunk_request);
+  one_slot = one_slot || M <= (size_t)w.chunk_rows;
   w.splits = joiner_bwd_splits(J, V, w.chunk_rows, bf16);
   w.n_db_rows = joiner_db_rows(w.chunk_rows);
   w.frame_off = c.take<int>((size_t)N + 1);

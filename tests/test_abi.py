@@ -76,6 +76,17 @@ def test_workspace_queries(L):
     assert L.rnnt_full_loss_workspace_size(2, 20, 5, 32, 16, N.RNNT_F32) > 0
 
 
+def test_backward_of_one_chunk_holds_one_slot_of_its_buffers(L):
+    """Rows of one chunk are not pipelined: d(logits) (fp32: in both its forms), h and the d dec pieces once."""
+    from paper_2206_13236_amd import _native as N
+    rows, J, V = 40 * 128, 512, 1024
+    for dt, words in ((N.RNNT_F32, 2), (N.RNNT_BF16, 1)):
+        one = rows * (2 * words * V * (2 if dt == N.RNNT_F32 else 1) + 2 * words * J + 4 * J)
+        args = (4, rows // 20, 10, 5, J, V, dt)
+        whole = L.rnnt_pruned_joiner_backward_ex_workspace_size(*args, rows)
+        assert whole < 1.1 * one + 4 * (32 * J * V + rows * (V // 32 + 64))  # and dW's and db's partials, the row info
+
+
 def test_simple_loss_workspace_holds_partial_sums_only_where_they_are_written(L):
     """The normaliser that forms Z in one kernel (U + 1 <= 128, V <= 1024) leaves no partial sums of [N, T, U + 1]."""
     N, T, U = 4, 900, 100
