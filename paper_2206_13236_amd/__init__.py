@@ -563,9 +563,11 @@ class PrunedRnntLoss:
         sizes, kept = self._size_cache.get(key), self._cache.get("ws_pruned")
         # a module's first step, or its first of these sizes: the stages up to the joiner are enqueued one by one, so
         # that what the later ones need is allocated, and the second stream set up, beside them and not before them
-        # (N = 32, T = 500, U = 100, V = 500, nothing allocated yet: 957 us with all of it before them, 763 so)
-        fresh = sizes is None or kept is None or kept.numel() != sizes[1] or kept.device != dev
-        n_simple = simple_loss_workspace_size(N, T, U, V) if fresh else sizes[0]
+        # (N = 32, T = 500, U = 100, V = 500, nothing allocated yet: 957 us with all of it before them, 763 so; a small
+        # batch, whose device time hides nothing, has fewer calls without: 206 against 222 at N = 2, T = 20, V = 16)
+        large = N * T * (U + 1) * V >= _OVERLAP_WORK
+        fresh = large and (sizes is None or kept is None or kept.numel() != sizes[1] or kept.device != dev)
+        n_simple = simple_loss_workspace_size(N, T, U, V) if fresh else self._sizes(key)[0]
         ws_s = self._buf("ws_simple", (n_simple,), torch.uint8, dev)
         ssc = self._buf("ssc", (N,), f32, dev)
         psc = self._buf("psc", (N,), f32, dev)
@@ -614,7 +616,7 @@ class PrunedRnntLoss:
         res.update(pruned_loss=o("pruned_loss", (N,)), pruned_px_occ=o("pruned_px_occ", band),
                    pruned_py_occ=o("pruned_py_occ", band), loss=o("loss", (N,)), total=o("total", ()))
         # the second stream's events cost more than what it would overlap on small batches
-        overlap = self.overlap and N * T * (U + 1) * V >= _OVERLAP_WORK
+        overlap = self.overlap and large
         side, (fork, lossev, join) = self._side_stream(dev) if overlap else (None, (None,) * 3)
         ptr = torch.Tensor.data_ptr
         p = RnntStep(
